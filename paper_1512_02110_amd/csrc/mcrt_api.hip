@@ -1766,14 +1766,16 @@ done:
 // (images != nullptr) or the gradient (dl, grad).
 int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_camera* cams, int n_side,
               const double* j, double* images, const double* dl, double* grad, hipStream_t stream,
-              const double* q = nullptr, double* counts = nullptr) {
+              const double* q = nullptr, double* counts = nullptr, double* keep_T = nullptr) {
     int rc = MC_OK;
     const int64_t n_vox = (int64_t)grid->nx * grid->ny * grid->nz;
     const int64_t n_cv = (int64_t)n_cams * n_vox;
     Scratch S;
     VoxArgs A;
     std::memset(&A, 0, sizeof(A));
-    size_t bytes = round256(sizeof(HostCam) * n_cams) + round256(sizeof(double) * n_cv) + 256;
+    int64_t max_rays = 0;  // of one camera
+    size_t bytes = round256(sizeof(HostCam) * n_cams) + round256(sizeof(VoxView) * n_cams) + 256;
+    if (!counts && !(grad && keep_T)) bytes += round256(sizeof(double) * n_cv);
     if (grad) bytes += round256(sizeof(double) * n_cv);
     CHECK_HIP(lib_alloc((void**)&S.base, bytes, stream));
     {
@@ -1802,6 +1804,8 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
         }
         A.cams = dcams;
         A.n_pix = off;
+        for (int i = 0; i < n_cams; ++i)
+            max_rays = std::max(max_rays, (int64_t)cams[i].width * cams[i].height * n_side * n_side);
     }
     A.nx = grid->nx;
     A.ny = grid->ny;
@@ -1813,16 +1817,24 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
     A.beta = beta;
     A.n_cams = n_cams;
     A.n_side = n_side;
-    A.T = S.take<double>(n_cv);
+    {
+        VoxView* views = S.take<VoxView>(n_cams);
+        CHECK_HIP(launch_vox_views(A, views, stream));
+        A.views = views;
+    }
     A.j = j;
     A.q = q;
     if (counts) {
         // ray counts only (the conditioning)
         CHECK_HIP(launch_fill_f64(counts, n_cv, stream));
-        CHECK_HIP(launch_vox_ray_counts(A, counts, stream));
+        CHECK_HIP(launch_vox_backproject(A, counts, true, max_rays, stream));
         goto done;
     }
-    CHECK_HIP(launch_vox_transmittance(A, stream));
+    // the images take T with its source factors, the gradient T alone; a loop
+    // that does both at one beta (keep_T) has the images' pass keep T as well
+    if (images) A.src = S.take<double>(n_cv);
+    A.T = keep_T ? keep_T : (grad ? S.take<double>(n_cv) : nullptr);
+    if (images || !keep_T) CHECK_HIP(launch_vox_transmittance(A, stream));
     if (images) {
         A.images = images;
         CHECK_HIP(launch_vox_project(A, stream));
@@ -1833,7 +1845,7 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
         A.grad = grad;
         CHECK_HIP(launch_fill_f64(A.B, n_cv, stream));
         CHECK_HIP(launch_fill_f64(grad, n_vox, stream));
-        CHECK_HIP(launch_vox_backproject(A, stream));
+        CHECK_HIP(launch_vox_backproject(A, A.B, false, max_rays, stream));
         CHECK_HIP(launch_vox_los_adjoint(A, stream));
     }
 done:
@@ -2250,17 +2262,18 @@ int mc_recover(const mc_grid* grid, double* beta, int n_cams, const mc_camera* c
     const int64_t n_cv = (int64_t)n_cams * n_vox;
     const int64_t n_pix = pixel_count(n_cams, cams);
     const bool fp32 = params->transport == MC_FP32;
-    // j, q: [camera][voxel]; img, dl: pixels; g, r: voxels; two scalars
-    const size_t bytes = round256(sizeof(double) * n_cv) * (conditioned ? 2 : 1) +
+    // j, q, T: [camera][voxel]; img, dl: pixels; g, r: voxels; two scalars
+    const size_t bytes = round256(sizeof(double) * n_cv) * (conditioned ? 3 : 2) +
                          round256(sizeof(double) * n_pix) * 2 + round256(sizeof(double) * n_vox) * 2 +
                          round256(sizeof(float) * n_vox) + 256 + 256;
     Scratch S;
-    double *j = nullptr, *q = nullptr, *img = nullptr, *dl = nullptr, *g = nullptr, *r = nullptr, *scal = nullptr;
+    double *j = nullptr, *q = nullptr, *T = nullptr, *img = nullptr, *dl = nullptr, *g = nullptr, *r = nullptr, *scal = nullptr;
     float* bf = nullptr;
     double h[2] = {0.0, 0.0};
     CHECK_HIP(lib_alloc((void**)&S.base, bytes, stream));
     j = S.take<double>(n_cv);
     if (conditioned) q = S.take<double>(n_cv);
+    T = S.take<double>(n_cv);
     img = S.take<double>(n_pix);
     dl = S.take<double>(n_pix);
     g = S.take<double>(n_vox);
@@ -2287,11 +2300,12 @@ int mc_recover(const mc_grid* grid, double* beta, int n_cams, const mc_camera* c
         }
         if (rc != MC_OK) goto done;
         for (int d = 0; d < n_gd; ++d) {
-            rc = run_voxel(grid, beta, n_cams, cams, rays_per_side, j, img, nullptr, nullptr, stream);
+            rc = run_voxel(grid, beta, n_cams, cams, rays_per_side, j, img, nullptr, nullptr, stream, nullptr,
+                           nullptr, T);
             if (rc != MC_OK) goto done;
             CHECK_HIP(launch_fill_f64(scal, 2, stream));
             CHECK_HIP(launch_image_residual(n_pix, img, measured, mask, dl, scal, stream));
-            rc = run_voxel(grid, beta, n_cams, cams, rays_per_side, j, nullptr, dl, g, stream, q);
+            rc = run_voxel(grid, beta, n_cams, cams, rays_per_side, j, nullptr, dl, g, stream, q, nullptr, T);
             if (rc != MC_OK) goto done;
             if (eta != 0.0)
                 CHECK_HIP(launch_reg(grid->nx, grid->ny, grid->nz, beta, w_layer, eta, r, g, scal + 1, stream));

@@ -244,29 +244,46 @@ hipError_t launch_voxel_finish(double* j, const double* L, int pitch, const Real
 
 // Voxelised model, deterministic part (mcrt_voxel.hip): FP64 throughout.
 // Cameras as HostCam (double), uploaded by k_vox_cams from kernel arguments.
+// Voxels around a camera's own on each side in its near box (k_vox_near).
+constexpr int VOX_NEAR = 5;
+
+// A camera as the gather over its rays sees it (k_vox_views).
+struct VoxView {
+    double M[9];        // world to camera axes: the inverse of the rays' R^T
+    double inv_far;     // 1 / the longest ray direction (qx, qy, 1) of the image, back-projected
+    double at[3];       // position in voxels
+    int on_face[3];     // whether that is a whole number
+    int cell[3];        // layer of the rays along an axis's faces (-1: outside the domain)
+    int lo[3], hi[3];   // near box: voxels [lo, hi)
+    int ok;             // 0: no such map, the rays are walked whole
+    int pad_;
+};
+
 struct VoxArgs {
     int nx, ny, nz;
     double dx, dy, dz;
     int64_t n_vox;
     const double* beta;
     const HostCam* cams;
+    const VoxView* views;
     int n_cams;
     int n_side;                 // sub-pixel rays per side (n_side^2 per pixel)
     int64_t n_pix;
-    double* T;                  // [camera][voxel] transmittance to the camera
+    double* T;                  // [camera][voxel] transmittance to the camera (nullable)
+    double* src;                // [camera][voxel] j beta T, for the images (nullable)
     const double* j;            // [camera][voxel]
     double* images;
     const double* dl;
-    double* B;                  // [camera][voxel] back-projected image gradient
+    double* B;                  // [camera][voxel] back-projected image gradient, then the lines' weights
     const double* q;            // [camera][voxel] weights of the camera terms (nullable)
     double* grad;
 };
 hipError_t launch_vox_cams(const CamChunk& chunk, HostCam* dev, hipStream_t s);
+hipError_t launch_vox_views(const VoxArgs& a, VoxView* views, hipStream_t s);
 hipError_t launch_vox_transmittance(const VoxArgs& a, hipStream_t s);
 hipError_t launch_vox_project(const VoxArgs& a, hipStream_t s);
-hipError_t launch_vox_backproject(const VoxArgs& a, hipStream_t s);
+hipError_t launch_vox_backproject(const VoxArgs& a, double* out, bool count, int64_t max_rays, hipStream_t s);
 hipError_t launch_vox_los_adjoint(const VoxArgs& a, hipStream_t s);
-hipError_t launch_vox_ray_counts(const VoxArgs& a, double* counts, hipStream_t s);
 hipError_t launch_vox_invert(double* x, int64_t n, hipStream_t s);
 hipError_t launch_reg(int nx, int ny, int nz, const double* beta, const double* w_layer, double eta, double* r,
                       double* grad, double* value, hipStream_t s);

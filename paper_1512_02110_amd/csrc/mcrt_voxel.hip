@@ -8,10 +8,18 @@
 // B_c = Pi_c^T dL/di_c, D_c(k, m) the length in voxel m of the line of sight
 // from the centre of voxel k to camera c.
 //
-// One thread per line of sight (T, gradient) or per pixel (images,
-// back-projection); each walks the voxels of its segment.  The images are
-// gathers (no atomics); B and the gradient are scatters with device FP64
-// atomics (at most a few times 1e8 per call for the benchmark grids).
+// T (k_vox_transmittance) and the images (k_vox_project) are ray walks that
+// gather.  B and the gradient scatter along rays that all meet at the camera:
+// as device atomics (past the L2, one line at a time) they took 3.9 + 2.6 ms
+// on the 64^3 grid with 9 cameras of 128^2 pixels and 2 x 2 rays.  So B is
+// gathered instead: every voxel sums over the rays of its footprint on the
+// image (k_vox_gather), except in a small box around each camera, where the
+// footprints grow to the whole image and the rays are walked into an LDS copy
+// of the box (k_vox_near); and the lines of sight are walked by tiles of
+// voxels into an LDS copy of the beam from the tile to the camera
+// (k_vox_los_adjoint).  Only voxels with j != 0 that some ray of the camera
+// can cross take part: T, B and the adjoint lines of the others only ever
+// multiply zero.
 #include <cmath>
 
 #include "mcrt_internal.hpp"
@@ -21,65 +29,118 @@ namespace {
 
 constexpr int VOX_BLOCK = 256;
 
-// Voxels of the segment p + t v, t in [0, tmax] (v unit), that lie in the
-// domain, in order: f(k, length inside k).  The segment is clipped to the
-// domain box first; a point on a face belongs to the voxel on the side the
-// segment moves into; ties between axes go to the lowest axis.  Crossings
-// are recomputed from the segment's start after every step (no accumulated
-// rounding).
-template <typename F>
-__device__ void seg_walk(const VoxArgs& A, double px, double py, double pz, double vx, double vy, double vz,
-                         double tmax, F&& f) {
-    const double p[3] = {px, py, pz};
-    const double v[3] = {vx, vy, vz};
-    const double d[3] = {A.dx, A.dy, A.dz};
-    const int n[3] = {A.nx, A.ny, A.nz};
-    double t0 = 0.0, t1 = tmax;
-    for (int a = 0; a < 3; ++a) {
-        const double len = n[a] * d[a];
-        if (v[a] == 0.0) {
-            if (p[a] < 0.0 || p[a] > len) return;
-            continue;
-        }
-        const double ta = (0.0 - p[a]) / v[a], tb = (len - p[a]) / v[a];
-        t0 = fmax(t0, fmin(ta, tb));
-        t1 = fmin(t1, fmax(ta, tb));
-    }
-    if (!(t1 > t0)) return;
-    int idx[3], step[3];
-    double tn[3];
-    for (int a = 0; a < 3; ++a) {
-        const double x = (p[a] + t0 * v[a]) / d[a];
-        int i = (int)floor(x);
-        if (v[a] < 0.0 && x == floor(x)) i -= 1;
-        i = i < 0 ? 0 : (i > n[a] - 1 ? n[a] - 1 : i);
-        idx[a] = i;
-        step[a] = v[a] > 0.0 ? 1 : (v[a] < 0.0 ? -1 : 0);
-        tn[a] = step[a] == 0 ? INFINITY : ((double)(i + (step[a] > 0 ? 1 : 0)) * d[a] - p[a]) / v[a];
-    }
-    const int64_t stride[3] = {1, (int64_t)A.nx, (int64_t)A.nx * A.ny};
-    int64_t k = idx[0] + stride[1] * idx[1] + stride[2] * idx[2];
-    double t = t0;
-    for (;;) {
-        int a = 0;
-        if (tn[1] < tn[a]) a = 1;
-        if (tn[2] < tn[a]) a = 2;
-        const bool last = tn[a] >= t1;
-        f(k, (last ? t1 : tn[a]) - t);
-        if (last) return;
-        t = tn[a];
-        idx[a] += step[a];
-        if (idx[a] < 0 || idx[a] >= n[a]) return;
-        k += step[a] * stride[a];
-        tn[a] = ((double)(idx[a] + (step[a] > 0 ? 1 : 0)) * d[a] - p[a]) / v[a];
+// One axis of a walk: the crossings are t0 + n dt for n = 0, 1, ... (one
+// fused multiply-add, so that nothing accumulates), the last of them, the exit
+// of the box, the same expression at its n: a walk ends at the box without
+// testing its indices.
+struct WalkAxis64 {
+    double t0, dt, n;
+    int i, s;
+};
+
+// Clip of [t0, t1] to the slab of faces lo, hi; false when a segment along the
+// faces lies outside it.
+__device__ __forceinline__ bool axis_clip(double p, double v, double iv, double d, int lo, int hi, double& t0,
+                                          double& t1) {
+    if (v == 0.0) return !(p < lo * d || p > hi * d);
+    const double ta = __fma_rn((double)lo, d, -p) * iv, tb = __fma_rn((double)hi, d, -p) * iv;
+    t0 = fmax(t0, fmin(ta, tb));
+    t1 = fmin(t1, fmax(ta, tb));
+    return true;
+}
+
+// The voxel of the entry point at t (a point on a face belongs to the voxel on
+// the side the segment moves into) and the crossings from there; t1 becomes
+// the exit of the box where that is earlier.
+__device__ __forceinline__ void axis_begin(WalkAxis64& a, double p, double v, double iv, double d, double t, int lo,
+                                           int hi, double& t1) {
+    const double x = (p + t * v) / d;
+    const double fl = floor(x);
+    int i = (int)fl;
+    if (v < 0.0 && x == fl) i -= 1;
+    i = i < lo ? lo : (i > hi - 1 ? hi - 1 : i);
+    a.i = i;
+    a.s = v > 0.0 ? 1 : (v < 0.0 ? -1 : 0);
+    a.n = 0.0;
+    a.t0 = INFINITY;
+    a.dt = 0.0;
+    if (a.s != 0) {
+        a.t0 = __fma_rn((double)(i + (a.s > 0 ? 1 : 0)), d, -p) * iv;
+        a.dt = fabs(d * iv);
+        t1 = fmin(t1, __fma_rn((double)(a.s > 0 ? hi - 1 - i : i - lo), a.dt, a.t0));
     }
 }
 
-__device__ void voxel_centre(const VoxArgs& A, int64_t k, double& x, double& y, double& z) {
-    const int64_t nxy = (int64_t)A.nx * A.ny;
-    x = ((double)(k % A.nx) + 0.5) * A.dx;
-    y = ((double)((k / A.nx) % A.ny) + 0.5) * A.dy;
-    z = ((double)(k / nxy) + 0.5) * A.dz;
+struct Box {
+    int x0, y0, z0, x1, y1, z1;  // voxels [x0, x1) x ...
+};
+
+// Voxels of the segment p + t v, t in [0, tmax] (v unit), that lie in the
+// box, in order: f(linear index, length inside), with IJK f(linear index, ix,
+// iy, iz, length inside).  The segment is clipped to the box first; ties between axes go to the
+// lowest axis.  Every choice between axes is a select of plain registers: the
+// state as arrays indexed by the axis lives in scratch memory, and with it and
+// a division per crossing the transmittances of 127 x 90 x 77 voxels to 16
+// cameras took 5.2 ms.  Instruction bound: about 25 a step.
+template <bool IJK, typename F>
+__device__ __forceinline__ void seg_walk(const VoxArgs& A, const Box& b, double px, double py, double pz, double vx,
+                                         double vy, double vz, double tmax, F&& f) {
+    const double ivx = 1.0 / vx, ivy = 1.0 / vy, ivz = 1.0 / vz;
+    double t0 = 0.0, t1 = tmax;
+    if (!axis_clip(px, vx, ivx, A.dx, b.x0, b.x1, t0, t1)) return;
+    if (!axis_clip(py, vy, ivy, A.dy, b.y0, b.y1, t0, t1)) return;
+    if (!axis_clip(pz, vz, ivz, A.dz, b.z0, b.z1, t0, t1)) return;
+    if (!(t1 > t0)) return;
+    WalkAxis64 X, Y, Z;
+    axis_begin(X, px, vx, ivx, A.dx, t0, b.x0, b.x1, t1);
+    axis_begin(Y, py, vy, ivy, A.dy, t0, b.y0, b.y1, t1);
+    axis_begin(Z, pz, vz, ivz, A.dz, t0, b.z0, b.z1, t1);
+    const int nxy = A.nx * A.ny;
+    int k = X.i + A.nx * Y.i + nxy * Z.i;
+    int ix = X.i, iy = Y.i, iz = Z.i;
+    const int kx = X.s, ky = Y.s * A.nx, kz = Z.s * nxy;
+    double t = t0, tx = X.t0, ty = Y.t0, tz = Z.t0;
+    for (;;) {
+        const double tn = fmin(tx, fmin(ty, tz));
+        const bool last = !(tn < t1);
+        if constexpr (IJK) f(k, ix, iy, iz, (last ? t1 : tn) - t);
+        else f(k, (last ? t1 : tn) - t);
+        t = tn;
+        const bool cx = tx == tn;
+        const bool cy = !cx && ty == tn;
+        const bool cz = !cx && !cy;
+        k += cx ? kx : (cy ? ky : kz);
+        if constexpr (IJK) {
+            ix += cx ? X.s : 0;
+            iy += cy ? Y.s : 0;
+            iz += cz ? Z.s : 0;
+        }
+        X.n += cx ? 1.0 : 0.0;
+        Y.n += cy ? 1.0 : 0.0;
+        Z.n += cz ? 1.0 : 0.0;
+        tx = __fma_rn(X.n, X.dt, X.t0);
+        ty = __fma_rn(Y.n, Y.dt, Y.t0);
+        tz = __fma_rn(Z.n, Z.dt, Z.t0);
+        // (no crossing of the box's end comes before t1: the index test only
+        // ends segments of non-finite numbers)
+        if (last || (unsigned)k >= (unsigned)A.n_vox) return;
+    }
+}
+
+__device__ __forceinline__ Box domain(const VoxArgs& A) { return Box{0, 0, 0, A.nx, A.ny, A.nz}; }
+
+__device__ __forceinline__ int64_t voxel_index(const VoxArgs& A, int ix, int iy, int iz) {
+    return ix + (int64_t)A.nx * (iy + (int64_t)A.ny * iz);
+}
+
+// Line of sight from the centre of voxel (ix, iy, iz) to the camera: its
+// voxels in the domain.
+template <bool IJK, typename F>
+__device__ __forceinline__ void sight_walk(const VoxArgs& A, const HostCam& cam, int ix, int iy, int iz, F&& f) {
+    const double x = (ix + 0.5) * A.dx, y = (iy + 0.5) * A.dy, z = (iz + 0.5) * A.dz;
+    const double Dx = cam.pos[0] - x, Dy = cam.pos[1] - y, Dz = cam.pos[2] - z;
+    const double len = sqrt(Dx * Dx + Dy * Dy + Dz * Dz);
+    if (len > 0.0) seg_walk<IJK>(A, domain(A), x, y, z, Dx / len, Dy / len, Dz / len, len, f);
 }
 
 // Camera of global pixel p (the last camera whose first pixel is <= p).
@@ -93,16 +154,21 @@ __device__ int camera_of_pixel(const VoxArgs& A, int64_t p) {
     return lo;
 }
 
-// Unit direction of sub-pixel ray (a, b) of pixel (row, col): through the
-// image point (col + (a + 1/2)/n, row + (b + 1/2)/n), back-projected
-// (world = R^T camera).
-__device__ void subpixel_dir(const HostCam& c, int row, int col, int a, int b, int n, double& vx, double& vy,
-                             double& vz) {
-    const double qx = ((double)col + (a + 0.5) / n - c.cx) / c.fx;
-    const double qy = ((double)row + (b + 0.5) / n - c.cy) / c.fy;
+// Direction (unnormalised) of the ray through the image point (u, v),
+// back-projected (world = R^T camera).
+__device__ __forceinline__ void image_dir(const HostCam& c, double u, double v, double& vx, double& vy, double& vz) {
+    const double qx = (u - c.cx) / c.fx;
+    const double qy = (v - c.cy) / c.fy;
     vx = c.R[0] * qx + c.R[3] * qy + c.R[6];
     vy = c.R[1] * qx + c.R[4] * qy + c.R[7];
     vz = c.R[2] * qx + c.R[5] * qy + c.R[8];
+}
+
+// Unit direction of sub-pixel ray (a, b) of pixel (row, col): through the
+// image point (col + (a + 1/2)/n, row + (b + 1/2)/n).
+__device__ __forceinline__ void subpixel_dir(const HostCam& c, int row, int col, int a, int b, int n, double& vx,
+                                             double& vy, double& vz) {
+    image_dir(c, (double)col + (a + 0.5) / n, (double)row + (b + 0.5) / n, vx, vy, vz);
     const double il = 1.0 / sqrt(vx * vx + vy * vy + vz * vz);
     vx *= il;
     vy *= il;
@@ -114,115 +180,592 @@ __global__ void k_vox_cams(CamChunk chunk, HostCam* dev) {
     if (i < chunk.n) dev[chunk.first + i] = chunk.c[i];
 }
 
-// T_c(k) for every camera and voxel (Eqs. taoKtoc, Tck).
-__global__ void __launch_bounds__(VOX_BLOCK) k_vox_transmittance(VoxArgs A) {
-    const int64_t n = (int64_t)A.n_cams * A.n_vox;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(i / A.n_vox);
-        const int64_t k = i % A.n_vox;
-        double x, y, z;
-        voxel_centre(A, k, x, y, z);
+// What the gather needs of each camera: M, the map from world to camera axes
+// that inverts the rays' back-projection R^T (R itself for a rotation), the
+// longest ray direction of the image, and the near box.  A camera without
+// such a map (a singular or badly conditioned R, which the rays do not need)
+// has ok = 0 and an empty near box: its rays are walked with device atomics.
+__global__ void k_vox_views(VoxArgs A, VoxView* views) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= A.n_cams) return;
+    const HostCam& cam = A.cams[c];
+    const double* R = cam.R;
+    VoxView V;
+    // cofactors: M = (R^T)^-1 = cof(R) / det(R)
+    double C[9];
+    C[0] = R[4] * R[8] - R[5] * R[7];
+    C[1] = R[5] * R[6] - R[3] * R[8];
+    C[2] = R[3] * R[7] - R[4] * R[6];
+    C[3] = R[2] * R[7] - R[1] * R[8];
+    C[4] = R[0] * R[8] - R[2] * R[6];
+    C[5] = R[1] * R[6] - R[0] * R[7];
+    C[6] = R[1] * R[5] - R[2] * R[4];
+    C[7] = R[2] * R[3] - R[0] * R[5];
+    C[8] = R[0] * R[4] - R[1] * R[3];
+    const double det = R[0] * C[0] + R[1] * C[1] + R[2] * C[2];
+    double off = 0.0;
+    for (int i = 0; i < 9; ++i) V.M[i] = C[i] / det;
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            // (M R^T)(i, j) = sum_k M(i, k) R(j, k)
+            const double e = V.M[3 * i] * R[3 * j] + V.M[3 * i + 1] * R[3 * j + 1] + V.M[3 * i + 2] * R[3 * j + 2];
+            off = fmax(off, fabs(e - (i == j ? 1.0 : 0.0)));
+            if (!isfinite(e)) off = INFINITY;
+        }
+    // |v| is convex over the image: its largest value is at a corner
+    double far2 = 0.0;
+    for (int k = 0; k < 4; ++k) {
+        double vx, vy, vz;
+        image_dir(cam, k & 1 ? cam.width : 0, k & 2 ? cam.height : 0, vx, vy, vz);
+        far2 = fmax(far2, vx * vx + vy * vy + vz * vz);
+    }
+    V.inv_far = 1.0 / sqrt(far2);
+    V.ok = off < 1e-12 && far2 > 0.0 && isfinite(far2) && V.inv_far > 0.0;
+    const double p[3] = {cam.pos[0] / A.dx, cam.pos[1] / A.dy, cam.pos[2] / A.dz};
+    const int n[3] = {A.nx, A.ny, A.nz};
+    for (int a = 0; a < 3; ++a) {
+        const double lo = floor(p[a]) - VOX_NEAR, hi = floor(p[a]) + VOX_NEAR + 1;
+        V.lo[a] = V.ok ? (int)fmin(fmax(lo, 0.0), (double)n[a]) : 0;
+        V.hi[a] = V.ok ? (int)fmin(fmax(hi, 0.0), (double)n[a]) : 0;
+    }
+    for (int a = 0; a < 3; ++a) {
+        // the walks' own reading of where the camera stands
+        const double len = n[a] * (a == 0 ? A.dx : (a == 1 ? A.dy : A.dz)), fl = floor(p[a]);
+        V.on_face[a] = p[a] == fl;
+        V.at[a] = p[a];
+        V.cell[a] = cam.pos[a] < 0.0 || cam.pos[a] > len ? -1 : (int)fmin(fmax(fl, 0.0), (double)(n[a] - 1));
+    }
+    for (int a = 0; a < 3; ++a)
+        if (V.lo[a] >= V.hi[a]) V.lo[0] = V.hi[0] = V.lo[1] = V.hi[1] = V.lo[2] = V.hi[2] = 0;
+    views[c] = V;
+}
+
+__device__ __forceinline__ bool in_near(const VoxView& V, int ix, int iy, int iz) {
+    return ix >= V.lo[0] && ix < V.hi[0] && iy >= V.lo[1] && iy < V.hi[1] && iz >= V.lo[2] && iz < V.hi[2];
+}
+
+// Sub-pixel columns s0 .. s1 and rows r0 .. r1 (as whole doubles) whose rays
+// can cross the voxel, which lies outside the near box; false when there are
+// none.  The box of the voxel in camera axes, q = M X as intervals; a point of
+// the view at distance r has qz >= r / |v|max, which keeps the ratios finite
+// where the box reaches behind the camera.  (Conservative: a ray of the range
+// that misses the voxel adds no length.)
+__device__ __forceinline__ bool footprint(const VoxArgs& A, const HostCam& cam, const VoxView& V, int ix, int iy,
+                                          int iz, double& s0, double& s1, double& r0, double& r1) {
+    const double hx = 0.5 * A.dx, hy = 0.5 * A.dy, hz = 0.5 * A.dz;
+    const double x = (ix + 0.5) * A.dx - cam.pos[0], y = (iy + 0.5) * A.dy - cam.pos[1],
+                 z = (iz + 0.5) * A.dz - cam.pos[2];
+    const double ex = fmax(fabs(x) - hx, 0.0), ey = fmax(fabs(y) - hy, 0.0), ez = fmax(fabs(z) - hz, 0.0);
+    const double zmin = sqrt(ex * ex + ey * ey + ez * ez) * V.inv_far * (1.0 - 1e-9);
+    const double qz = V.M[6] * x + V.M[7] * y + V.M[8] * z;
+    const double wz = fabs(V.M[6]) * hx + fabs(V.M[7]) * hy + fabs(V.M[8]) * hz;
+    if (!(qz + wz > zmin)) return false;
+    const double i0 = 1.0 / fmax(qz - wz, zmin), i1 = 1.0 / (qz + wz);
+    const double n = (double)A.n_side;
+    const double qx = V.M[0] * x + V.M[1] * y + V.M[2] * z;
+    const double wx = fabs(V.M[0]) * hx + fabs(V.M[1]) * hy + fabs(V.M[2]) * hz;
+    const double xa = qx - wx, xb = qx + wx;
+    const double u0 = n * (cam.cx + cam.fx * (xa * (xa < 0.0 ? i0 : i1))) - 0.5;
+    const double u1 = n * (cam.cx + cam.fx * (xb * (xb > 0.0 ? i0 : i1))) - 0.5;
+    s0 = fmax(ceil(u0 - 1e-3 - 1e-9 * fabs(u0)), 0.0);
+    s1 = fmin(floor(u1 + 1e-3 + 1e-9 * fabs(u1)), n * cam.width - 1.0);
+    if (!(s0 <= s1)) return false;
+    const double qy = V.M[3] * x + V.M[4] * y + V.M[5] * z;
+    const double wy = fabs(V.M[3]) * hx + fabs(V.M[4]) * hy + fabs(V.M[5]) * hz;
+    const double ya = qy - wy, yb = qy + wy;
+    const double v0 = n * (cam.cy + cam.fy * (ya * (ya < 0.0 ? i0 : i1))) - 0.5;
+    const double v1 = n * (cam.cy + cam.fy * (yb * (yb > 0.0 ? i0 : i1))) - 0.5;
+    r0 = fmax(ceil(v0 - 1e-3 - 1e-9 * fabs(v0)), 0.0);
+    r1 = fmin(floor(v1 + 1e-3 + 1e-9 * fabs(v1)), n * cam.height - 1.0);
+    return r0 <= r1;
+}
+
+// A block takes VOX_CHUNK voxels of a camera, consecutive or (SPREAD) in runs
+// of 64 spread over the whole grid: the voxels next to a camera hold most of
+// its rays, and a block of consecutive ones there runs on alone.  (512 or 256
+// voxels: the lists get too short, the gather 7-33% slower.)  Voxel of the
+// block's offset o:
+constexpr int VOX_CHUNK = 1024;
+
+template <bool SPREAD>
+__device__ __forceinline__ int64_t chunk_voxel(int o) {
+    return SPREAD ? ((int64_t)(o >> 6) * gridDim.x + blockIdx.x) * 64 + (o & 63)
+                  : (int64_t)blockIdx.x * VOX_CHUNK + o;
+}
+
+// The block's voxels that `take` accepts, as offsets in its LDS list (in no
+// particular order): the lines that are walked are then dense in the lanes,
+// where a third of the voxels hold cloud and a camera sees a part of them.
+template <bool SPREAD, typename P>
+__device__ __forceinline__ int list_voxels(const VoxArgs& A, uint16_t* s_list, int* s_n, P&& take) {
+    if (threadIdx.x == 0) *s_n = 0;
+    __syncthreads();
+    for (int o = threadIdx.x; o < VOX_CHUNK; o += VOX_BLOCK) {
+        const int64_t k = chunk_voxel<SPREAD>(o);
+        const bool in = k < A.n_vox && take((int)k);
+        const unsigned long long m = __ballot(in);
+        int base = 0;
+        if (m && __lane_id() == 0) base = atomicAdd(s_n, __popcll(m));
+        base = __shfl(base, 0);
+        if (in) s_list[base + __popcll(m & __lanemask_lt())] = (uint16_t)o;
+    }
+    __syncthreads();
+    return *s_n;
+}
+
+__device__ __forceinline__ void voxel_of(const VoxArgs& A, int k, int& ix, int& iy, int& iz) {
+    ix = k % A.nx;
+    const int r = k / A.nx;
+    iy = r % A.ny;
+    iz = r / A.ny;
+}
+
+// Some ray of the camera can cross the voxel.
+__device__ __forceinline__ bool visible(const VoxArgs& A, const HostCam& cam, const VoxView& V, int k) {
+    int ix, iy, iz;
+    double s0, s1, r0, r1;
+    voxel_of(A, k, ix, iy, iz);
+    return !V.ok || in_near(V, ix, iy, iz) || footprint(A, cam, V, ix, iy, iz, s0, s1, r0, r1);
+}
+
+// T_c(k) (Eqs. taoKtoc, Tck) of the voxels with j != 0 that the camera's rays
+// can cross, and for the images T j beta (src); the other voxels get 0, which
+// is what they contribute.  Bound by the gathers of beta: the block's voxels
+// are spread over the grid (shorter last lines) while beta fits an XCD's 4 MB
+// of L2, and consecutive past it (64^3, 9 cameras: 113 us spread, 143
+// consecutive; 127 x 90 x 77, 16 cameras: 480 and 350).
+template <bool SPREAD>
+__global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_transmittance(VoxArgs A) {
+    __shared__ uint16_t s_list[VOX_CHUNK];
+    __shared__ int s_n;
+    for (int c = blockIdx.y; c < A.n_cams; c += gridDim.y) {
         const HostCam& cam = A.cams[c];
-        const double Dx = cam.pos[0] - x, Dy = cam.pos[1] - y, Dz = cam.pos[2] - z;
-        const double len = sqrt(Dx * Dx + Dy * Dy + Dz * Dz);
-        double tau = 0.0;
-        if (len > 0.0)
-            seg_walk(A, x, y, z, Dx / len, Dy / len, Dz / len, len,
-                     [&](int64_t m, double l) { tau += A.beta[m] * l; });
-        A.T[i] = exp(-tau);
+        const VoxView& V = A.views[c];
+        const int64_t off = (int64_t)c * A.n_vox;
+        const int n = list_voxels<SPREAD>(A, s_list, &s_n, [&](int k) {
+            const bool on = A.j[off + k] != 0.0 && visible(A, cam, V, k);
+            if (!on && A.T) A.T[off + k] = 0.0;
+            if (!on && A.src) A.src[off + k] = 0.0;
+            return on;
+        });
+        for (int e = threadIdx.x; e < n; e += VOX_BLOCK) {
+            const int k = (int)chunk_voxel<SPREAD>(s_list[e]);
+            int ix, iy, iz;
+            voxel_of(A, k, ix, iy, iz);
+            // (a voxel's term is added a step after its fetch is issued)
+            double tau = 0.0, bp = 0.0, lp = 0.0;
+            sight_walk<false>(A, cam, ix, iy, iz, [&](int m, double l) {
+                tau += bp * lp;
+                bp = A.beta[m];
+                lp = l;
+            });
+            const double T = exp(-(tau + bp * lp));
+            if (A.T) A.T[off + k] = T;
+            if (A.src) A.src[off + k] = A.j[off + k] * A.beta[k] * T;
+        }
+        __syncthreads();
     }
 }
 
-// i_c(p) = 1/(n^2 V) sum_rho sum_k l_rho(k) j_c(k) beta(k) T_c(k).
-__global__ void __launch_bounds__(VOX_BLOCK) k_vox_project(VoxArgs A) {
+// i_c(p) = 1/(n^2 V) sum_rho sum_k l_rho(k) src_c(k), src = j beta T.  One
+// lane per sub-pixel ray (tpp lanes a pixel, at most a block's), summed in LDS:
+// with one lane per pixel the images of 9 cameras of 128^2 pixels were two
+// wavefronts a SIMD (64^3, 2 x 2 rays: 92 us, 270 before).
+__global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_project(VoxArgs A) {
+    __shared__ double s_acc[VOX_BLOCK];
     const double scale = 1.0 / ((double)A.n_side * A.n_side * A.dx * A.dy * A.dz);
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < A.n_pix;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const int c = camera_of_pixel(A, p);
-        const HostCam& cam = A.cams[c];
-        const int64_t lp = p - cam.pix_off;
-        const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
-        const double* jc = A.j + (int64_t)c * A.n_vox;
-        const double* Tc = A.T + (int64_t)c * A.n_vox;
+    const int n2 = A.n_side * A.n_side;
+    const int tpp = n2 < VOX_BLOCK ? n2 : VOX_BLOCK;
+    const int per = VOX_BLOCK / tpp;
+    const int slot = threadIdx.x / tpp, sub = threadIdx.x % tpp;
+    for (int64_t p0 = (int64_t)blockIdx.x * per; p0 < A.n_pix; p0 += (int64_t)gridDim.x * per) {
+        const int64_t p = p0 + slot;
+        const bool in = slot < per && p < A.n_pix;
         double acc = 0.0;
-        for (int b = 0; b < A.n_side; ++b)
-            for (int a = 0; a < A.n_side; ++a) {
+        if (in) {
+            const int c = camera_of_pixel(A, p);
+            const HostCam& cam = A.cams[c];
+            const int64_t lp = p - cam.pix_off;
+            const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
+            const double* src = A.src + (int64_t)c * A.n_vox;
+            for (int r = sub; r < n2; r += tpp) {
                 double vx, vy, vz;
-                subpixel_dir(cam, row, col, a, b, A.n_side, vx, vy, vz);
-                seg_walk(A, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
-                         [&](int64_t k, double l) { acc += l * jc[k] * A.beta[k] * Tc[k]; });
+                subpixel_dir(cam, row, col, r % A.n_side, r / A.n_side, A.n_side, vx, vy, vz);
+                double sp = 0.0, lp = 0.0;
+                seg_walk<false>(A, domain(A), cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
+                                [&](int k, double l) {
+                                    acc += lp * sp;
+                                    sp = src[k];
+                                    lp = l;
+                                });
+                acc += lp * sp;
             }
-        A.images[p] = acc * scale;
+        }
+        s_acc[threadIdx.x] = acc;
+        __syncthreads();
+        if (in && sub == 0) {
+            for (int i = 1; i < tpp; ++i) acc += s_acc[threadIdx.x + i];
+            A.images[p] = acc * scale;
+        }
+        __syncthreads();
     }
 }
 
-// B_c = Pi_c^T dl_c: every sub-pixel ray scatters dl(p) l / (n^2 V).
-__global__ void __launch_bounds__(VOX_BLOCK) k_vox_backproject(VoxArgs A) {
+// Rays of the cameras inside their near boxes: B_c += g l (Pi^T dl), or, with
+// COUNT, += 1 for every ray longer than eps in the voxel.  A block walks a
+// range of one camera's rays and adds its LDS copy of the box at the end (the
+// first voxels take every ray of the image, so device atomics would queue on
+// them).  A camera without a view has its whole rays walked, with device
+// atomics.
+template <bool COUNT>
+__global__ void __launch_bounds__(VOX_BLOCK) k_vox_near(VoxArgs A, double* out) {
+    constexpr int W = 2 * VOX_NEAR + 1;
+    __shared__ double s_b[W * W * W];
+    const double scale = COUNT ? 1.0 : 1.0 / ((double)A.n_side * A.n_side * A.dx * A.dy * A.dz);
+    const double eps = 1e-9 * fmin(A.dx, fmin(A.dy, A.dz));
+    const int n = A.n_side, n2 = n * n;
+    for (int c = blockIdx.y; c < A.n_cams; c += gridDim.y) {
+        const HostCam& cam = A.cams[c];
+        const VoxView V = A.views[c];
+        double* Bc = out + (int64_t)c * A.n_vox;
+        const Box box = V.ok ? Box{V.lo[0], V.lo[1], V.lo[2], V.hi[0], V.hi[1], V.hi[2]} : domain(A);
+        if (box.x0 >= box.x1) continue;
+        const int64_t rays = (int64_t)cam.width * cam.height * n2;
+        if ((int64_t)blockIdx.x * VOX_BLOCK >= rays) continue;
+        for (int i = threadIdx.x; i < W * W * W; i += VOX_BLOCK) s_b[i] = 0.0;
+        __syncthreads();
+        for (int64_t q = (int64_t)blockIdx.x * VOX_BLOCK + threadIdx.x; q < rays;
+             q += (int64_t)gridDim.x * VOX_BLOCK) {
+            const int64_t lp = q / n2;
+            const int r = (int)(q % n2);
+            const double g = COUNT ? 1.0 : A.dl[cam.pix_off + lp] * scale;
+            if (g == 0.0) continue;
+            double vx, vy, vz;
+            subpixel_dir(cam, (int)(lp / cam.width), (int)(lp % cam.width), r % n, r / n, n, vx, vy, vz);
+            seg_walk<true>(A, box, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
+                           [&](int k, int ix, int iy, int iz, double l) {
+                               if (COUNT && !(l > eps)) return;
+                               const double x = COUNT ? 1.0 : g * l;
+                               if (V.ok)
+                                   atomicAdd(&s_b[(ix - box.x0) + W * ((iy - box.y0) + W * (iz - box.z0))], x);
+                               else
+                                   unsafeAtomicAdd(Bc + k, x);
+                           });
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; V.ok && i < W * W * W; i += VOX_BLOCK) {
+            const double x = s_b[i];
+            if (x != 0.0)
+                unsafeAtomicAdd(Bc + voxel_index(A, box.x0 + i % W, box.y0 + (i / W) % W, box.z0 + i / (W * W)), x);
+        }
+        __syncthreads();
+    }
+}
+
+// A voxel's faces relative to the camera.  A ray along the faces of an axis
+// runs through the voxels of one layer, the camera's (sx, sy, sz: this one).
+// The faces of an axis on which the camera stands on a face are counted from
+// that face, so that this one is at exactly 0 and a ray leaves it to the side
+// that it moves into, as the walks have it, however small that motion is.
+struct Slab {
+    double x0, x1, y0, y1, z0, z1;
+    bool sx, sy, sz;
+};
+
+__device__ __forceinline__ double face_from(const VoxView& V, int a, int i, double d, double p) {
+    return V.on_face[a] ? ((double)i - V.at[a]) * d : __fma_rn((double)i, d, -p);
+}
+
+// 1/x to the last bit or two without the scaling of an IEEE division (x = 0
+// is the callers').
+__device__ __forceinline__ double fast_rcp(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = __fma_rn(__fma_rn(-x, r, 1.0), r, r);
+    return __fma_rn(__fma_rn(-x, r, 1.0), r, r);
+}
+
+__device__ __forceinline__ void slab_axis(double a0, double a1, bool same, double v, double& tin, double& tout) {
+    const double iv = fast_rcp(v);
+    const double ta = a0 * iv, tb = a1 * iv;
+    const bool still = v == 0.0;
+    tin = fmax(tin, still ? (same ? 0.0 : INFINITY) : fmin(ta, tb));
+    tout = fmin(tout, still ? INFINITY : fmax(ta, tb));
+}
+
+// Length of the ray from the camera along (vx, vy, vz), not normalised, in the
+// voxel: the overlap of its crossings of the three slabs.
+__device__ __forceinline__ double slab_length(const Slab& B, double vx, double vy, double vz) {
+    double tin = 0.0, tout = INFINITY;
+    slab_axis(B.x0, B.x1, B.sx, vx, tin, tout);
+    slab_axis(B.y0, B.y1, B.sy, vy, tin, tout);
+    slab_axis(B.z0, B.z1, B.sz, vz, tin, tout);
+    return tout > tin ? (tout - tin) * sqrt(vx * vx + vy * vy + vz * vz) : 0.0;
+}
+
+// B_c of the voxels outside the near box, gathered over the footprint of each
+// on the image: a few rays a voxel far from the camera (one lane), hundreds
+// next to the near box (a wavefront, 8 x 8 rays at a time).  No atomics, and
+// the sum of a voxel does not depend on the launch.  Bound by instructions
+// (VALU 33% of the slots: the lanes' footprints differ): 64^3, 9 cameras of
+// 128^2, 2 x 2 rays 302 us with the near pass's 58, against 3.86 ms of device
+// atomics; 127 x 90 x 77, 16 cameras of 160 x 120 741 + 84 us against 7.6 ms.
+// COUNT: the number of rays longer than eps.  Otherwise B is used at once: grad(k) += q T j B, and B
+// (scratch) becomes the weight w = T beta j B of the voxel's line of sight.
+constexpr double VOX_LIGHT = 64.0;
+
+template <bool COUNT>
+__device__ __forceinline__ void voxel_done(const VoxArgs& A, double* out, int c, int k, double B) {
+    const int64_t i = (int64_t)c * A.n_vox + k;
+    if (COUNT) {
+        out[i] = B;
+        return;
+    }
+    const double bj = B * A.j[i];
+    const double T = A.T[i];
+    out[i] = bj == 0.0 ? 0.0 : T * A.beta[k] * bj;
+    if (bj != 0.0) unsafeAtomicAdd(A.grad + k, (A.q ? A.q[i] : 1.0) * T * bj);
+}
+
+template <bool COUNT>
+__global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_gather(VoxArgs A, double* out) {
+    __shared__ uint16_t s_list[VOX_CHUNK], s_heavy[VOX_CHUNK];
+    __shared__ double s_frac[64];
+    __shared__ int s_n, s_nh;
     const double scale = 1.0 / ((double)A.n_side * A.n_side * A.dx * A.dy * A.dz);
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < A.n_pix;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const double g = A.dl[p] * scale;
-        if (g == 0.0) continue;
-        const int c = camera_of_pixel(A, p);
+    const double eps = 1e-9 * fmin(A.dx, fmin(A.dy, A.dz));
+    const double n = (double)A.n_side, in = 1.0 / n;
+    if (threadIdx.x < A.n_side) s_frac[threadIdx.x] = (threadIdx.x + 0.5) / n;
+    for (int c = blockIdx.y; c < A.n_cams; c += gridDim.y) {
         const HostCam& cam = A.cams[c];
-        const int64_t lp = p - cam.pix_off;
-        const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
-        double* Bc = A.B + (int64_t)c * A.n_vox;
-        for (int b = 0; b < A.n_side; ++b)
-            for (int a = 0; a < A.n_side; ++a) {
-                double vx, vy, vz;
-                subpixel_dir(cam, row, col, a, b, A.n_side, vx, vy, vz);
-                seg_walk(A, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
-                         [&](int64_t k, double l) { unsafeAtomicAdd(Bc + k, g * l); });
+        const VoxView& V = A.views[c];
+        const int64_t off = (int64_t)c * A.n_vox;
+        const double* dl = A.dl + (COUNT ? 0 : cam.pix_off);
+        const double ifx = 1.0 / cam.fx, ify = 1.0 / cam.fy;
+        if (threadIdx.x == 0) s_nh = 0;
+        const int n_list = list_voxels<true>(A, s_list, &s_n, [&](int k) {
+            if (!COUNT && !(A.j[off + k] != 0.0)) {
+                out[off + k] = 0.0;  // (the near pass may have added to it)
+                return false;
             }
+            int ix, iy, iz;
+            voxel_of(A, k, ix, iy, iz);
+            if (!V.ok || in_near(V, ix, iy, iz)) {
+                // accumulated by the near pass
+                if (!COUNT) voxel_done<COUNT>(A, out, c, k, out[off + k]);
+                return false;
+            }
+            double s0, s1, r0, r1;
+            return footprint(A, cam, V, ix, iy, iz, s0, s1, r0, r1);
+        });
+        auto slab = [&](int ix, int iy, int iz) {
+            return Slab{face_from(V, 0, ix, A.dx, cam.pos[0]), face_from(V, 0, ix + 1, A.dx, cam.pos[0]),
+                        face_from(V, 1, iy, A.dy, cam.pos[1]), face_from(V, 1, iy + 1, A.dy, cam.pos[1]),
+                        face_from(V, 2, iz, A.dz, cam.pos[2]), face_from(V, 2, iz + 1, A.dz, cam.pos[2]),
+                        ix == V.cell[0], iy == V.cell[1], iz == V.cell[2]};
+        };
+        // sum over the rays (s, r) of the range, strided
+        auto gather = [&](const Slab& B, double s0, double s1, double r0, double r1, double step) {
+            double acc = 0.0;
+            for (double r = r0; r <= r1; r += step) {
+                const double row = floor((r + 0.5) * in);
+                const double qy = (row + s_frac[(int)(r - row * n)] - cam.cy) * ify;
+                const double ox = __fma_rn(cam.R[3], qy, cam.R[6]), oy = __fma_rn(cam.R[4], qy, cam.R[7]),
+                             oz = __fma_rn(cam.R[5], qy, cam.R[8]);
+                for (double s = s0; s <= s1; s += step) {
+                    const double col = floor((s + 0.5) * in);
+                    const double qx = (col + s_frac[(int)(s - col * n)] - cam.cx) * ifx;
+                    const double l = slab_length(B, __fma_rn(cam.R[0], qx, ox), __fma_rn(cam.R[1], qx, oy),
+                                                 __fma_rn(cam.R[2], qx, oz));
+                    if (COUNT) {
+                        if (l > eps) acc += 1.0;
+                    } else if (l > 0.0) {
+                        acc += dl[(int)row * cam.width + (int)col] * scale * l;
+                    }
+                }
+            }
+            return acc;
+        };
+        for (int e = threadIdx.x; e < n_list; e += VOX_BLOCK) {
+            const int k = (int)chunk_voxel<true>(s_list[e]);
+            int ix, iy, iz;
+            double s0, s1, r0, r1;
+            voxel_of(A, k, ix, iy, iz);
+            footprint(A, cam, V, ix, iy, iz, s0, s1, r0, r1);
+            if ((s1 - s0 + 1.0) * (r1 - r0 + 1.0) > VOX_LIGHT) {
+                s_heavy[atomicAdd(&s_nh, 1)] = s_list[e];
+                continue;
+            }
+            voxel_done<COUNT>(A, out, c, k, gather(slab(ix, iy, iz), s0, s1, r0, r1, 1.0));
+        }
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        for (int e = threadIdx.x >> 6; e < s_nh; e += VOX_BLOCK / 64) {
+            const int k = (int)chunk_voxel<true>(s_heavy[e]);
+            int ix, iy, iz;
+            double s0, s1, r0, r1;
+            voxel_of(A, k, ix, iy, iz);
+            footprint(A, cam, V, ix, iy, iz, s0, s1, r0, r1);
+            double acc = gather(slab(ix, iy, iz), s0 + (lane & 7), s1, r0 + (lane >> 3), r1, 8.0);
+            for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+            if (lane == 0) voxel_done<COUNT>(A, out, c, k, acc);
+        }
+        __syncthreads();
     }
 }
 
-// grad(k) += T j B; then the line of sight from the centre of k to the
-// camera takes -T beta j B times its length in every voxel it crosses.
-__global__ void __launch_bounds__(VOX_BLOCK) k_vox_los_adjoint(VoxArgs A) {
-    const int64_t n = (int64_t)A.n_cams * A.n_vox;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const double bj = A.B[i] * A.j[i];
-        if (bj == 0.0) continue;
-        const int c = (int)(i / A.n_vox);
-        const int64_t k = i % A.n_vox;
-        const double T = A.T[i];
+// The line of sight from the centre of k to the camera takes -w l (w = T beta
+// j B of k, in A.B) in every voxel it crosses.  A block walks the lines of a
+// tile of 8 x 8 x 8 voxels into an LDS copy of the beam from the tile to the
+// camera: per slice of voxels along the beam's longest axis, the rectangle
+// that the lines cross, which narrows from the tile to one voxel.  The beam
+// is added to the gradient at the end, so that a device atomic stands for
+// every voxel of the beam instead of every crossing of every line.  Bound by
+// instructions (VALU 50%): 64^3, 9 cameras 268 us against 2.64 ms with an
+// atomic per crossing, 127 x 90 x 77, 16 cameras 0.89 against 4.1 ms.  Slices
+// past the LDS copy's room, and a crossing that rounding puts outside its
+// rectangle, go to the gradient directly.
+constexpr int LOS_TILE = 8;
+constexpr int LOS_BLOCK = LOS_TILE * LOS_TILE * LOS_TILE;
+constexpr int LOS_SLICES = 256;
+constexpr int LOS_CELLS = 4608;  // 36 KB: with the tables four blocks a CU
+
+__global__ void __launch_bounds__(LOS_BLOCK, 6) k_vox_los_adjoint(VoxArgs A, int tx, int ty) {
+    __shared__ double s_b[LOS_CELLS];
+    __shared__ int4 s_sl[LOS_SLICES];  // a slice's rectangle: first u, first v, width (0: no room), first cell
+    __shared__ int s_h[LOS_SLICES];    // and height
+    __shared__ int s_any, s_cells;
+    const int t = threadIdx.x;
+    const int bx = (int)(blockIdx.x % tx) * LOS_TILE, by = (int)((blockIdx.x / tx) % ty) * LOS_TILE,
+              bz = (int)(blockIdx.x / ((unsigned)tx * ty)) * LOS_TILE;
+    const int l0 = t % LOS_TILE, l1 = (t / LOS_TILE) % LOS_TILE, l2 = t / (LOS_TILE * LOS_TILE);
+    const int n[3] = {A.nx, A.ny, A.nz};
+    const int lo[3] = {bx, by, bz};
+    const int hi[3] = {min(bx + LOS_TILE, A.nx), min(by + LOS_TILE, A.ny), min(bz + LOS_TILE, A.nz)};
+    for (int c = blockIdx.y; c < A.n_cams; c += gridDim.y) {
+        const HostCam& cam = A.cams[c];
+        // the camera in voxel units; the beam's axis a and the other two, u and v
+        const double P[3] = {cam.pos[0] / A.dx, cam.pos[1] / A.dy, cam.pos[2] / A.dz};
+        const double far_x = fabs(P[0] - 0.5 * (lo[0] + hi[0])), far_y = fabs(P[1] - 0.5 * (lo[1] + hi[1])),
+                     far_z = fabs(P[2] - 0.5 * (lo[2] + hi[2]));
+        const int a = far_z >= far_x && far_z >= far_y ? 2 : (far_y >= far_x ? 1 : 0);
+        // the lanes of a wavefront span the beam's axis and one other, so that
+        // at a step they stand in eight slices and fewer of them meet in one
+        // voxel near the camera
+        const int ix = bx + (a == 0 ? l0 : l1), iy = by + (a == 1 ? l0 : (a == 0 ? l1 : l2)),
+                  iz = bz + (a == 2 ? l0 : l2);
+        const bool in = ix < A.nx && iy < A.ny && iz < A.nz;
+        const double w = in ? A.B[(int64_t)c * A.n_vox + voxel_index(A, ix, iy, iz)] : 0.0;
+        if (t == 0) s_any = 0;
+        __syncthreads();
+        if (w != 0.0) s_any = 1;
+        __syncthreads();
+        if (!s_any) continue;
+        // slices 0 .. n_s - 1: a0 + s, from the tile's first voxel or the
+        // camera's, whichever is lower, nearest LOS_SLICES to the tile
+        const double Pa = a == 0 ? P[0] : (a == 1 ? P[1] : P[2]);
+        const int la = a == 0 ? lo[0] : (a == 1 ? lo[1] : lo[2]), ha = a == 0 ? hi[0] : (a == 1 ? hi[1] : hi[2]);
+        const int na = a == 0 ? n[0] : (a == 1 ? n[1] : n[2]);
+        const double fa = floor(Pa);
+        int a0 = fa < la ? (int)fmax(fa, 0.0) : la;
+        int a1 = fa >= ha ? (int)fmin(fa + 1.0, (double)na) : ha;
+        if (a1 - a0 > LOS_SLICES) {
+            if (a0 < la) a0 = a1 - LOS_SLICES;
+            else a1 = a0 + LOS_SLICES;
+        }
+        const int n_s = a1 - a0;
+        for (int s = t; s < n_s; s += LOS_BLOCK) {
+            int r0[2], r1[2];
+            for (int d = 0; d < 2; ++d) {
+                const int ax = d == 0 ? (a == 0 ? 1 : 0) : (a == 2 ? 1 : 2);
+                const double Pd = ax == 0 ? P[0] : (ax == 1 ? P[1] : P[2]);
+                const int ld = ax == 0 ? lo[0] : (ax == 1 ? lo[1] : lo[2]);
+                const int hd = ax == 0 ? hi[0] : (ax == 1 ? hi[1] : hi[2]);
+                const int nd = ax == 0 ? n[0] : (ax == 1 ? n[1] : n[2]);
+                double m0 = INFINITY, m1 = -INFINITY;
+                if (Pa > la - 1.0 && Pa < ha + 1.0) {
+                    // the camera is level with the tile: the hull of both
+                    m0 = fmin(ld + 0.5, Pd);
+                    m1 = fmax(hd - 0.5, Pd);
+                } else {
+                    // the position X + (P - X)(z - Xa)/(Pa - Xa) is monotone
+                    // in X, Xa and z each: its extremes are at their ends
+                    for (int e = 0; e < 8; ++e) {
+                        const double X = e & 1 ? hd - 0.5 : ld + 0.5, Xa = e & 2 ? ha - 0.5 : la + 0.5;
+                        const double z = a0 + s + (e & 4 ? 1 : 0);
+                        const double f = fmin(fmax((z - Xa) / (Pa - Xa), 0.0), 1.0);
+                        const double x = X + (Pd - X) * f;
+                        m0 = fmin(m0, x);
+                        m1 = fmax(m1, x);
+                    }
+                }
+                r0[d] = (int)fmin(fmax(floor(m0 - 1e-6), 0.0), (double)nd);
+                r1[d] = (int)fmin(fmax(floor(m1 + 1e-6) + 1.0, 0.0), (double)nd);
+            }
+            s_sl[s] = make_int4(r0[0], r0[1], max(r1[0] - r0[0], 0), 0);
+            s_h[s] = max(r1[1] - r0[1], 0);
+        }
+        __syncthreads();
+        if (t < 64) {
+            // first cells of the slices (four a lane): the slices in front of
+            // the first one that does not fit get room
+            int m[LOS_SLICES / 64], sum = 0;
+            for (int i = 0; i < LOS_SLICES / 64; ++i) {
+                const int s = t * (LOS_SLICES / 64) + i;
+                m[i] = s < n_s ? (int)min((int64_t)s_sl[s].z * s_h[s], (int64_t)(LOS_CELLS + 1)) : 0;
+                sum += m[i];
+            }
+            int end = sum;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(end, o);
+                end += t >= o ? x : 0;
+            }
+            int o = end - sum, used = 0;
+            for (int i = 0; i < LOS_SLICES / 64; ++i) {
+                const int s = t * (LOS_SLICES / 64) + i;
+                if (s < n_s) {
+                    s_sl[s].w = o;
+                    if (o + m[i] > LOS_CELLS) s_sl[s].z = s_h[s] = 0;
+                    else used = o + m[i];
+                }
+                o += m[i];
+            }
+            for (int i = 32; i > 0; i >>= 1) used = max(used, __shfl_xor(used, i));
+            if (t == 0) s_cells = used;
+        }
+        __syncthreads();
+        const int cells = s_cells;
+        for (int i = t; i < cells; i += LOS_BLOCK) s_b[i] = 0.0;
+        __syncthreads();
         const double* qc = A.q ? A.q + (int64_t)c * A.n_vox : nullptr;
-        unsafeAtomicAdd(A.grad + k, (qc ? qc[k] : 1.0) * T * bj);
-        const double w = T * A.beta[k] * bj;
-        if (w == 0.0) continue;
-        double x, y, z;
-        voxel_centre(A, k, x, y, z);
-        const HostCam& cam = A.cams[c];
-        const double Dx = cam.pos[0] - x, Dy = cam.pos[1] - y, Dz = cam.pos[2] - z;
-        const double len = sqrt(Dx * Dx + Dy * Dy + Dz * Dz);
-        if (!(len > 0.0)) continue;
-        seg_walk(A, x, y, z, Dx / len, Dy / len, Dz / len, len,
-                 [&](int64_t m, double l) { unsafeAtomicAdd(A.grad + m, -(qc ? qc[m] : 1.0) * w * l); });
-    }
-}
-
-// Sec. 6: counts[c][k] += 1 for every sub-pixel ray of camera c whose length
-// in voxel k exceeds 1e-9 of the shortest voxel edge (a ray that only grazes
-// an edge or a corner is not counted, whatever the rounding).
-__global__ void __launch_bounds__(VOX_BLOCK) k_vox_ray_counts(VoxArgs A, double* counts) {
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < A.n_pix;
-         p += (int64_t)gridDim.x * blockDim.x) {
-        const int c = camera_of_pixel(A, p);
-        const HostCam& cam = A.cams[c];
-        const int64_t lp = p - cam.pix_off;
-        const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
-        double* Cc = counts + (int64_t)c * A.n_vox;
-        const double eps = 1e-9 * fmin(A.dx, fmin(A.dy, A.dz));
-        for (int b = 0; b < A.n_side; ++b)
-            for (int a = 0; a < A.n_side; ++a) {
-                double vx, vy, vz;
-                subpixel_dir(cam, row, col, a, b, A.n_side, vx, vy, vz);
-                seg_walk(A, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY, [&](int64_t k, double l) {
-                    if (l > eps) unsafeAtomicAdd(Cc + k, 1.0);
-                });
+        if (w != 0.0)
+            sight_walk<true>(A, cam, ix, iy, iz, [&](int m, int jx, int jy, int jz, double l) {
+                const int s = (a == 0 ? jx : (a == 1 ? jy : jz)) - a0;
+                const int u = a == 0 ? jy : jx, v = a == 2 ? jy : jz;
+                if ((unsigned)s < (unsigned)n_s) {
+                    const int4 r = s_sl[s];
+                    const int du = u - r.x, dv = v - r.y;
+                    if ((unsigned)du < (unsigned)r.z && (unsigned)dv < (unsigned)s_h[s]) {
+                        atomicAdd(&s_b[r.w + du + r.z * dv], w * l);
+                        return;
+                    }
+                }
+                unsafeAtomicAdd(A.grad + m, -(qc ? qc[m] : 1.0) * w * l);
+            });
+        __syncthreads();
+        // a wavefront per slice: its cells in order of u
+        for (int s = t >> 6; s < n_s; s += LOS_BLOCK / 64) {
+            const int4 r = s_sl[s];
+            const int m = r.z * s_h[s];
+            for (int i = t & 63; i < m; i += 64) {
+                const double x = s_b[r.w + i];
+                if (x == 0.0) continue;
+                const int u = r.x + i % r.z, v = r.y + i / r.z, z = a0 + s;
+                const int64_t k = a == 0 ? voxel_index(A, z, u, v)
+                                         : (a == 1 ? voxel_index(A, u, z, v) : voxel_index(A, u, v, z));
+                unsafeAtomicAdd(A.grad + k, -(qc ? qc[k] : 1.0) * x);
             }
+        }
+        __syncthreads();
     }
 }
 
@@ -371,24 +914,49 @@ hipError_t launch_vox_cams(const CamChunk& chunk, HostCam* dev, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Grid of the kernels that take a range of voxels (or rays) and a camera.
+static dim3 cam_grid(int64_t blocks, int n_cams) { return dim3((unsigned)(blocks > 0 ? blocks : 1), (unsigned)n_cams); }
+
+static int64_t vox_chunks(const VoxArgs& a) { return (a.n_vox + VOX_CHUNK - 1) / VOX_CHUNK; }
+
+hipError_t launch_vox_views(const VoxArgs& a, VoxView* views, hipStream_t s) {
+    hipLaunchKernelGGL(k_vox_views, dim3((a.n_cams + 63) / 64), dim3(64), 0, s, a, views);
+    return hipGetLastError();
+}
+
 hipError_t launch_vox_transmittance(const VoxArgs& a, hipStream_t s) {
-    const int64_t n = (int64_t)a.n_cams * a.n_vox;
-    if (n > 0) hipLaunchKernelGGL(k_vox_transmittance, dim3(grid_for(n)), dim3(VOX_BLOCK), 0, s, a);
+    const dim3 grid = cam_grid(vox_chunks(a), a.n_cams);
+    if (a.n_vox * (int64_t)sizeof(double) <= (int64_t)4 << 20)
+        hipLaunchKernelGGL(k_vox_transmittance<true>, grid, dim3(VOX_BLOCK), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_vox_transmittance<false>, grid, dim3(VOX_BLOCK), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_vox_project(const VoxArgs& a, hipStream_t s) {
-    if (a.n_pix > 0) hipLaunchKernelGGL(k_vox_project, dim3(grid_for(a.n_pix)), dim3(VOX_BLOCK), 0, s, a);
+    const int64_t n2 = (int64_t)a.n_side * a.n_side;
+    const int64_t per = VOX_BLOCK / (n2 < VOX_BLOCK ? n2 : VOX_BLOCK);
+    if (a.n_pix > 0) {
+        const int64_t blocks = (a.n_pix + per - 1) / per;
+        hipLaunchKernelGGL(k_vox_project, dim3((unsigned)(blocks < 1048576 ? blocks : 1048576)), dim3(VOX_BLOCK), 0, s,
+                           a);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_vox_backproject(const VoxArgs& a, hipStream_t s) {
-    if (a.n_pix > 0) hipLaunchKernelGGL(k_vox_backproject, dim3(grid_for(a.n_pix)), dim3(VOX_BLOCK), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_vox_ray_counts(const VoxArgs& a, double* counts, hipStream_t s) {
-    if (a.n_pix > 0) hipLaunchKernelGGL(k_vox_ray_counts, dim3(grid_for(a.n_pix)), dim3(VOX_BLOCK), 0, s, a, counts);
+// B (out, zeroed): near boxes, then the gather, which also turns B into the
+// gradient's local term and the lines' weights (count: into the ray counts).
+hipError_t launch_vox_backproject(const VoxArgs& a, double* out, bool count, int64_t max_rays, hipStream_t s) {
+    // 8 rays a thread, so that a block's box is added once per 2048 rays
+    const int64_t near = (max_rays + 8 * VOX_BLOCK - 1) / (8 * VOX_BLOCK);
+    const dim3 g_near = cam_grid(near < 4096 ? near : 4096, a.n_cams), g_far = cam_grid(vox_chunks(a), a.n_cams);
+    if (count) {
+        hipLaunchKernelGGL(k_vox_near<true>, g_near, dim3(VOX_BLOCK), 0, s, a, out);
+        hipLaunchKernelGGL(k_vox_gather<true>, g_far, dim3(VOX_BLOCK), 0, s, a, out);
+    } else {
+        hipLaunchKernelGGL(k_vox_near<false>, g_near, dim3(VOX_BLOCK), 0, s, a, out);
+        hipLaunchKernelGGL(k_vox_gather<false>, g_far, dim3(VOX_BLOCK), 0, s, a, out);
+    }
     return hipGetLastError();
 }
 
@@ -435,8 +1003,9 @@ hipError_t launch_recovery_sums(int64_t n, const double* b, const double* t, dou
 }
 
 hipError_t launch_vox_los_adjoint(const VoxArgs& a, hipStream_t s) {
-    const int64_t n = (int64_t)a.n_cams * a.n_vox;
-    if (n > 0) hipLaunchKernelGGL(k_vox_los_adjoint, dim3(grid_for(n)), dim3(VOX_BLOCK), 0, s, a);
+    const int tx = (a.nx + LOS_TILE - 1) / LOS_TILE, ty = (a.ny + LOS_TILE - 1) / LOS_TILE;
+    const int64_t tiles = (int64_t)tx * ty * ((a.nz + LOS_TILE - 1) / LOS_TILE);
+    hipLaunchKernelGGL(k_vox_los_adjoint, cam_grid(tiles, a.n_cams), dim3(LOS_BLOCK), 0, s, a, tx, ty);
     return hipGetLastError();
 }
 
