@@ -1430,7 +1430,7 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
     mix_tape = mode == MODE_MIXGRAD && A.tape;
     CHECK_HIP(transport_occupancy<Real>(A, A.tape && (mode != MODE_MIXGRAD || mix_tape) ? MODE_TAPE : launch_mode,
                                         tally, &per_cu));
-    if (mode != MODE_TRACE) {
+    if (mode != MODE_TRACE && mode != MODE_BMC) {  // (those walk every voxel)
         uint32_t* mask = S.take<uint32_t>(mask_words);
         A.mask = mask;
         if (A.air_step)

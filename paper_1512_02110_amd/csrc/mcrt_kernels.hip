@@ -1655,141 +1655,384 @@ __global__ void __launch_bounds__(BLOCK) k_trace(KArgs<Real> A) {
 }
 
 // ---------------------------------------------------------------------------
-// Backward Monte Carlo (Sec. 2.1.4): one packet per lane.
+// Backward Monte Carlo (Sec. 2.1.4).
 
-// Transmittance from the collision towards the sun, Eq. (ble): exp(-tau) to
-// the top face, 0 when the path leaves through a side face (light enters
-// through the top face only, as in the forward method).
+// Packet id p * n_pp + i of global pixel p: leg 0 gives the point of the
+// pixel and the first free path; the camera centre and the back-projected
+// direction are in double; the packet enters the domain where its ray does
+// (false when it does not).
 template <typename Real>
-__device__ __forceinline__ double sun_transmittance(const KArgs<Real>& A, const Photon<Real>& ph) {
+__device__ __forceinline__ bool bmc_launch(const KArgs<Real>& A, uint64_t id, int64_t& gp, Photon<Real>& ph) {
+    const double L[3] = {(double)A.G.nx * (double)A.G.dx, (double)A.G.ny * (double)A.G.dy,
+                         (double)A.G.nz * (double)A.G.dz};
+    const double dv[3] = {(double)A.G.dx, (double)A.G.dy, (double)A.G.dz};
+    const int nv[3] = {A.G.nx, A.G.ny, A.G.nz};
+    gp = (int64_t)(id / A.n_pp);
+    int lo = 0, hi = A.n_cams - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (A.hcams[mid].pix_off <= gp) lo = mid;
+        else hi = mid - 1;
+    }
+    const HostCam& cam = A.hcams[lo];
+    const int64_t lp = gp - cam.pix_off;
+    const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
+    const uint4 r = draw(A.seed, id, 0u);
+    const double qx = ((double)col + (double)uniform01<Real>(r.x) - cam.cx) / cam.fx;
+    const double qy = ((double)row + (double)uniform01<Real>(r.y) - cam.cy) / cam.fy;
+    double d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) d[a] = cam.R[a] * qx + cam.R[3 + a] * qy + cam.R[6 + a];
+    const double il = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+    double t0 = 0.0, t1 = INFINITY;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        d[a] *= il;
+        if (d[a] == 0.0) {
+            if (cam.pos[a] < 0.0 || cam.pos[a] > L[a]) t1 = -1.0;
+            continue;
+        }
+        const double ta = (0.0 - cam.pos[a]) / d[a], tb = (L[a] - cam.pos[a]) / d[a];
+        t0 = fmax(t0, fmin(ta, tb));
+        t1 = fmin(t1, fmax(ta, tb));
+    }
+    if (!(t1 > t0)) return false;
+    int iv[3];
+    Real fv[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double f = (cam.pos[a] + t0 * d[a]) / dv[a];
+        int i = (int)floor(f);
+        if (d[a] < 0.0 && f == floor(f)) i -= 1;
+        i = i < 0 ? 0 : (i > nv[a] - 1 ? nv[a] - 1 : i);
+        iv[a] = i;
+        fv[a] = (Real)(f - (double)i);
+    }
+    ph.ix = iv[0];
+    ph.iy = iv[1];
+    ph.iz = iv[2];
+    ph.fx = fv[0];
+    ph.fy = fv[1];
+    ph.fz = fv[2];
+    ph.wx = (Real)d[0];
+    ph.wy = (Real)d[1];
+    ph.wz = (Real)d[2];
+    ph.weight = (Real)1;
+    ph.taustar = -m_log((Real)1 - uniform01<Real>(r.z));
+    ph.t_exit = (Real)0;
+    ph.s = 0;
+    ph.pid = id;
+    ph.air = 0;
+    return true;
+}
+
+// Whether the collision's path towards the sun, Eq. (ble), leaves through the
+// top face (light enters there only, as in the forward method).
+template <typename Real>
+__device__ __forceinline__ bool sun_seen(const KArgs<Real>& A, const Photon<Real>& ph) {
     const Real sx = -A.wsx, sy = -A.wsy, sz = -A.wsz;
     const double x = absolute(ph.ix, ph.fx, A.G.dx), y = absolute(ph.iy, ph.fy, A.G.dy);
     const double z = absolute(ph.iz, ph.fz, A.G.dz);
     const double lx = (double)A.G.nx * (double)A.G.dx, ly = (double)A.G.ny * (double)A.G.dy;
     const double tz = ((double)A.G.nz * (double)A.G.dz - z) / (double)sz;
     const double xe = x + tz * (double)sx, ye = y + tz * (double)sy;
-    if (!(xe >= 0.0 && xe <= lx && ye >= 0.0 && ye <= ly)) return 0.0;
-    ConnWalk<Real> W;
-    const Real texit = conn_begin(W, A.G, ph.ix, ph.iy, ph.iz, ph.fx, ph.fy, ph.fz, sx, sy, sz);
-    if (texit < (Real)0) return 0.0;
-    double tau = 0.0;
-    for (;;) {
-        bool cx, cy, cz;
-        const Real tn = conn_next(W, cx, cy, cz);
-        const bool last = tn >= texit;
-        tau += (double)A.beta[W.k] * (double)((last ? texit : tn) - W.t);
-        if (last) break;
-        conn_cross(W, tn, cx, cy, cz);
-        if ((uint32_t)W.k >= (uint32_t)A.n_vox) break;
-    }
-    return exp(-tau);
+    return xe >= 0.0 && xe <= lx && ye >= 0.0 && ye <= ly;
 }
 
-// Packet id p * n_pp + i of global pixel p: leg 0 gives the point of the
-// pixel and the first free path; the camera centre and the back-projected
-// direction are in double; the packet enters the domain where its ray does.
+// Persistent wavefronts.  A lane's packet alternates between its flights and,
+// at every collision, the walk towards the sun; both are the same voxel
+// step, so all lanes of a wavefront step together whichever walk they are on,
+// and the lanes at an end wait until BMC_WAIT of them are (40 is as fast, 24
+// and 16 up to 4 and 13% slower), when their collisions, estimates, new
+// flights and new packets are done together.  Three wavefronts a SIMD: held to
+// 128 VGPRs for four, the FP64 launches and collisions spill and the kernel is
+// 13-30% slower.
+//
+// One packet per lane, with a loop of its own for each flight and walk that
+// the wavefront runs until its longest lane is through, took 2.90 ms for 16
+// packets per pixel of 9 cameras of 128^2 on a 64^3 cloud and 10.3 ms for 64;
+// this takes 1.31 and 4.16 ms (5.0e9 collisions/s).  A launch ends with its
+// longest packet, a serial chain of collisions: with one packet per pixel that
+// chain is the whole 0.38 ms (0.55 before; 0.65 without the idle lanes'
+// help).  Bound by instruction issue and that chain.
+enum { BMC_NONE = 0, BMC_FLIGHT, BMC_SUN, BMC_HIT, BMC_LIT, BMC_GONE, BMC_DONE, BMC_GO };
+constexpr uint32_t BMC_WAIT = 32;
+
+// Launched packets of a wavefront.
 template <typename Real>
-__global__ void __launch_bounds__(BLOCK) k_bmc(KArgs<Real> A) {
+struct BmcList {
+    uint32_t vox[WAVE];
+    Real fx[WAVE], fy[WAVE], fz[WAVE];
+    Real wx[WAVE], wy[WAVE], wz[WAVE];
+    Real star[WAVE];
+    int32_t pix[WAVE];
+    uint64_t id[WAVE];
+    // estimates walked by another lane: their prefactors (with the point and
+    // the packet's lane in the fields above), and per lane the sum of those
+    // finished and the number under way
+    double pre[WAVE], sum[WAVE];
+    uint32_t open[WAVE];
+};
+
+template <typename Real>
+__global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
     __shared__ unsigned long long s_st[ST_N];
+    __shared__ BmcList<Real> s_list[BLOCK / WAVE];
+    BmcList<Real>& Q = s_list[threadIdx.x / WAVE];
+    Q.sum[__lane_id()] = 0.0;
+    Q.open[__lane_id()] = 0u;
+    uint32_t n_list = 0, owner = __lane_id();
+    bool lit = false;          // the collision's path to the sun is to be walked
     if (threadIdx.x < ST_N) s_st[threadIdx.x] = 0ull;
     __syncthreads();
-    uint32_t n_ev = 0;
-    uint64_t vfree = 0;
     const Real sx = -A.wsx, sy = -A.wsy, sz = -A.wsz;
     const uint64_t total = (uint64_t)A.n_pix * A.n_pp;
-    const double L[3] = {(double)A.G.nx * (double)A.G.dx, (double)A.G.ny * (double)A.G.dy,
-                         (double)A.G.nz * (double)A.G.dz};
-    const double dv[3] = {(double)A.G.dx, (double)A.G.dy, (double)A.G.dz};
-    const int nv[3] = {A.G.nx, A.G.ny, A.G.nz};
-    for (uint64_t id = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; id < total;
-         id += (uint64_t)gridDim.x * blockDim.x) {
-        const int64_t gp = (int64_t)(id / A.n_pp);
-        int lo = 0, hi = A.n_cams - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (A.hcams[mid].pix_off <= gp) lo = mid;
-            else hi = mid - 1;
-        }
-        const HostCam& cam = A.hcams[lo];
-        const int64_t lp = gp - cam.pix_off;
-        const int row = (int)(lp / cam.width), col = (int)(lp % cam.width);
-        const uint4 r = draw(A.seed, id, 0u);
-        const double qx = ((double)col + (double)uniform01<Real>(r.x) - cam.cx) / cam.fx;
-        const double qy = ((double)row + (double)uniform01<Real>(r.y) - cam.cy) / cam.fy;
-        double d[3];
-        for (int a = 0; a < 3; ++a) d[a] = cam.R[a] * qx + cam.R[3 + a] * qy + cam.R[6 + a];
-        const double il = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        double t0 = 0.0, t1 = INFINITY;
-        for (int a = 0; a < 3; ++a) {
-            d[a] *= il;
-            if (d[a] == 0.0) {
-                if (cam.pos[a] < 0.0 || cam.pos[a] > L[a]) t1 = -1.0;
-                continue;
-            }
-            const double ta = (0.0 - cam.pos[a]) / d[a], tb = (L[a] - cam.pos[a]) / d[a];
-            t0 = fmax(t0, fmin(ta, tb));
-            t1 = fmin(t1, fmax(ta, tb));
-        }
-        if (!(t1 > t0)) {
-            atomicAdd(&s_st[ST_SIDE], 1ull);
-            continue;
-        }
-        Photon<Real> ph;
-        int iv[3];
-        Real fv[3];
-        for (int a = 0; a < 3; ++a) {
-            const double f = (cam.pos[a] + t0 * d[a]) / dv[a];
-            int i = (int)floor(f);
-            if (d[a] < 0.0 && f == floor(f)) i -= 1;
-            i = i < 0 ? 0 : (i > nv[a] - 1 ? nv[a] - 1 : i);
-            iv[a] = i;
-            fv[a] = (Real)(f - (double)i);
-        }
-        ph.ix = iv[0];
-        ph.iy = iv[1];
-        ph.iz = iv[2];
-        ph.fx = fv[0];
-        ph.fy = fv[1];
-        ph.fz = fv[2];
-        ph.wx = (Real)d[0];
-        ph.wy = (Real)d[1];
-        ph.wz = (Real)d[2];
-        ph.weight = (Real)1;
-        ph.taustar = -m_log((Real)1 - uniform01<Real>(r.z));
-        ph.t_exit = (Real)0;
-        ph.s = 0;
-        ph.pid = id;
-        ph.air = 0;
-        double packet = 0.0;
-        for (;;) {
-            const int left = free_flight(A, (const uint32_t*)nullptr, ph, vfree, 0xffffffffu);
-            if (left) {
-                atomicAdd(&s_st[ST_TOP + left - 1], 1ull);
-                break;
-            }
+    uint32_t n_ev = 0;
+    uint64_t vfree_w = 0;  // counted per wavefront
+    uint64_t pool_next = 0, pool_end = 0;
+    Photon<Real> ph;
+    ph.ix = ph.iy = ph.iz = 0;
+    ph.air = 0;
+    int32_t gp = 0;
+    double packet = 0.0;
+    double tau_s = 0.0;        // optical depth towards the sun
+    double pre = 0.0;          // albedo I_s P of the estimate under way
+    int fate = -1;             // of the collision under way
+    int state = BMC_NONE;
+    bool exhausted = false;
+    // the walk under way; tau and its end star of a flight, texit of a sun walk
+    WalkRegs<Real> W;
+    W.ix = W.iy = W.iz = W.k = W.sx = W.sy = W.sz = W.kx = W.ky = W.kz = 0;
+    W.sfx = W.sfy = W.sfz = W.rx = W.ry = W.rz = W.gx = W.gy = W.gz = W.tx = W.ty = W.tz = W.t = (Real)0;
+    Real tau = (Real)0, star = (Real)0, texit = (Real)0, b = (Real)0, b_hit = (Real)1;
+    for (;;) {
+        if (state == BMC_HIT) {
+            // the flight's collision: its point, the estimate and the next direction
+            const Real tc = W.t + (star - tau) / b_hit;
+            ph.fx = walk_frac(ph.fx, W.sfx, W.rx, ph.wx, A.G.idx, tc);
+            ph.fy = walk_frac(ph.fy, W.sfy, W.ry, ph.wy, A.G.idy, tc);
+            ph.fz = walk_frac(ph.fz, W.sfz, W.rz, ph.wz, A.G.idz, tc);
+            ph.ix = W.ix;
+            ph.iy = W.iy;
+            ph.iz = W.iz;
             ph.s += 1;
             ++n_ev;
-            const double t = sun_transmittance(A, ph);
-            if (t > 0.0) {
-                const Real cosang = ph.wx * sx + ph.wy * sy + ph.wz * sz;
-                packet += (double)A.albedo * (double)ph.weight * (double)hg_phase(A.g, cosang) * t;
+            lit = sun_seen(A, ph);
+            const Real cosang = ph.wx * sx + ph.wy * sy + ph.wz * sz;
+            pre = (double)A.albedo * (double)ph.weight * (double)hg_phase(A.g, cosang);
+            owner = __lane_id();
+            fate = after_collision(A, ph);
+        }
+        if (exhausted && n_list == 0u) {
+            // no packets are left: lanes without one take the walks of the
+            // others' estimates, so that a long packet goes on with its next
+            // flight meanwhile (a launch ends with its longest packet)
+            const unsigned long long give = __ballot(lit), none = __ballot(state == BMC_NONE);
+            const uint32_t n = min((uint32_t)__popcll(give), (uint32_t)__popcll(none));
+            if (lit && lanes_below(give) < n) {
+                const uint32_t j = lanes_below(give);
+                Q.vox[j] = (uint32_t)ph.ix | ((uint32_t)ph.iy << 11) | ((uint32_t)ph.iz << 22);
+                Q.fx[j] = ph.fx;
+                Q.fy[j] = ph.fy;
+                Q.fz[j] = ph.fz;
+                Q.pre[j] = pre;
+                Q.pix[j] = (int32_t)__lane_id();
+                Q.open[__lane_id()] += 1u;
+                lit = false;
             }
-            const int fate = after_collision(A, ph);
-            if (fate >= 0) {
-                atomicAdd(&s_st[fate == MC_FATE_CAP ? ST_CAP : ST_RR], 1ull);
-                break;
+            __builtin_amdgcn_wave_barrier();
+            if (state == BMC_NONE && lanes_below(none) < n) {
+                const uint32_t j = lanes_below(none), v = Q.vox[j];
+                ph.ix = (int)(v & 2047u);
+                ph.iy = (int)((v >> 11) & 2047u);
+                ph.iz = (int)(v >> 22);
+                ph.fx = Q.fx[j];
+                ph.fy = Q.fy[j];
+                ph.fz = Q.fz[j];
+                pre = Q.pre[j];
+                owner = (uint32_t)Q.pix[j];
+                lit = true;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (lit) {
+            ConnWalk<Real> C;
+            texit = conn_begin(C, A.G, ph.ix, ph.iy, ph.iz, ph.fx, ph.fy, ph.fz, sx, sy, sz);
+            W.k = C.k;
+            W.kx = C.kx;
+            W.ky = C.ky;
+            W.kz = C.kz;
+            W.sfx = C.sfx;
+            W.sfy = C.sfy;
+            W.sfz = C.sfz;
+            W.rx = C.rx;
+            W.ry = C.ry;
+            W.rz = C.rz;
+            W.gx = C.gx;
+            W.gy = C.gy;
+            W.gz = C.gz;
+            W.tx = C.tx;
+            W.ty = C.ty;
+            W.tz = C.tz;
+            W.t = C.t;
+            star = (Real)INFINITY;
+            tau_s = 0.0;
+            b = A.beta[W.k];
+            // (a walk that cannot start adds nothing)
+            pre = texit < (Real)0 ? 0.0 : pre;
+            state = texit < (Real)0 ? BMC_LIT : BMC_SUN;
+            lit = false;
+        } else if (state == BMC_HIT) {
+            pre = 0.0;
+            state = BMC_LIT;
+        }
+        if (state == BMC_LIT) {
+            const double tr = pre != 0.0 ? exp(-tau_s) : 0.0;
+            const double x = tr > 0.0 ? pre * tr : 0.0;
+            if (owner == __lane_id()) {
+                packet += x;
+                if (fate >= 0) atomicAdd(&s_st[fate == MC_FATE_CAP ? ST_CAP : ST_RR], 1ull);
+                state = fate >= 0 ? BMC_DONE : BMC_GO;
+            } else {
+                atomicAdd(&Q.sum[owner], x);
+                atomicSub(&Q.open[owner], 1u);
+                state = BMC_NONE;
+            }
+        } else if (state == BMC_GONE) {
+            // the axis that left its range tells the face (none: a flight that
+            // could not start counts as a side)
+            const bool z = (unsigned)W.iz >= (unsigned)A.G.nz;
+            atomicAdd(&s_st[z ? (W.iz < 0 ? ST_BOTTOM : ST_TOP) : ST_SIDE], 1ull);
+            state = BMC_DONE;
+        }
+        if (state == BMC_DONE && Q.open[__lane_id()] == 0u) {
+            packet += Q.sum[__lane_id()];
+            Q.sum[__lane_id()] = 0.0;
+            if (packet != 0.0) {
+                unsafeAtomicAdd(A.img + gp, packet / (double)A.n_pp);
+                if (A.img_m2) unsafeAtomicAdd(A.img_m2 + gp, packet * packet / (double)A.n_pp);
+            }
+            state = BMC_NONE;
+        }
+        // new packets, launched 64 at a time into the wavefront's LDS list (a
+        // few lanes need one at a time, and a launch is mostly FP64 divisions)
+        for (;;) {
+            const unsigned long long need = __ballot(state == BMC_NONE);
+            if (need == 0ull) break;
+            if (n_list == 0u) {
+                if (exhausted) break;
+                const uint64_t id = wave_fetch(A.work, A.fetch_block, ~0ull, pool_next, pool_end);
+                Photon<Real> np;
+                int64_t p = 0;
+                const bool in = id < total && bmc_launch(A, id, p, np);
+                if (id < total && !in) atomicAdd(&s_st[ST_SIDE], 1ull);
+                exhausted = __ballot(id >= total) != 0ull;
+                const unsigned long long m = __ballot(in);
+                if (in) {
+                    const uint32_t j = lanes_below(m);
+                    Q.vox[j] = (uint32_t)np.ix | ((uint32_t)np.iy << 11) | ((uint32_t)np.iz << 22);
+                    Q.fx[j] = np.fx;
+                    Q.fy[j] = np.fy;
+                    Q.fz[j] = np.fz;
+                    Q.wx[j] = np.wx;
+                    Q.wy[j] = np.wy;
+                    Q.wz[j] = np.wz;
+                    Q.star[j] = np.taustar;
+                    Q.pix[j] = (int32_t)p;
+                    Q.id[j] = id;
+                }
+                n_list = (uint32_t)__popcll(m);
+                __builtin_amdgcn_wave_barrier();
+                continue;
+            }
+            const uint32_t take = min((uint32_t)__popcll(need), n_list);
+            if (state == BMC_NONE && lanes_below(need) < take) {
+                const uint32_t j = n_list - 1u - lanes_below(need);
+                const uint32_t v = Q.vox[j];
+                ph.ix = (int)(v & 2047u);
+                ph.iy = (int)((v >> 11) & 2047u);
+                ph.iz = (int)(v >> 22);
+                ph.fx = Q.fx[j];
+                ph.fy = Q.fy[j];
+                ph.fz = Q.fz[j];
+                ph.wx = Q.wx[j];
+                ph.wy = Q.wy[j];
+                ph.wz = Q.wz[j];
+                ph.weight = (Real)1;
+                ph.taustar = Q.star[j];
+                ph.s = 0;
+                ph.pid = Q.id[j];
+                gp = Q.pix[j];
+                packet = 0.0;
+                state = BMC_GO;
+            }
+            n_list -= take;
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (state == BMC_GO) {
+            if (walk_begin(W, A.G, ph.ix, ph.iy, ph.iz, ph.fx, ph.fy, ph.fz, ph.wx, ph.wy, ph.wz)) {
+                tau = (Real)0;
+                star = ph.taustar;
+                texit = (Real)INFINITY;
+                b = A.beta[W.k];
+                state = BMC_FLIGHT;
+            } else {
+                state = BMC_GONE;
             }
         }
-        if (packet != 0.0) {
-            unsafeAtomicAdd(A.img + gp, packet / (double)A.n_pp);
-            if (A.img_m2) unsafeAtomicAdd(A.img_m2 + gp, packet * packet / (double)A.n_pp);
+        if (__ballot(state != BMC_NONE) == 0ull) break;
+        const bool flight = state == BMC_FLIGHT;
+        bool act = flight || state == BMC_SUN;
+        const uint32_t n_act = (uint32_t)__popcll(__ballot(act));
+        const uint32_t keep = n_act - min(BMC_WAIT, (n_act + 1u) / 2u);
+        const unsigned long long m_f = __ballot(flight);
+        for (;;) {
+            const unsigned long long m = __ballot(act);
+            if ((uint32_t)__popcll(m) <= keep) break;
+            vfree_w += (uint32_t)__popcll(m & m_f);
+            if (act) {
+                // branch free: a flight has no texit and a sun walk no star
+                // (both infinite).  The next voxel's fetch goes out before
+                // this one's extinction is needed, and the crossing is
+                // committed unless the photon collides first.
+                bool cx, cy, cz;
+                const Real tn = walk_next(W, cx, cy, cz);
+                const bool last = tn >= texit;
+                const Real l = (last ? texit : tn) - W.t;
+                const int kx = W.kx, ky = W.ky, kz = W.kz, sx_ = W.sx, sy_ = W.sy, sz_ = W.sz;
+                const int k = W.k + (cx ? kx : (cy ? ky : kz));
+                const int ix = W.ix + (cx ? sx_ : 0), iy = W.iy + (cy ? sy_ : 0), iz = W.iz + (cz ? sz_ : 0);
+                const bool away = flight ? (unsigned)ix >= (unsigned)A.G.nx || (unsigned)iy >= (unsigned)A.G.ny ||
+                                               (unsigned)iz >= (unsigned)A.G.nz
+                                         : last || (uint32_t)k >= (uint32_t)A.n_vox;
+                const Real bn = A.beta[away ? (uint32_t)A.n_vox : (uint32_t)k];
+                const Real t2 = tau + b * l;
+                const bool hit = b > (Real)0 && t2 >= star;
+                tau_s += (double)b * (double)l;
+                tau = hit ? tau : t2;
+                b_hit = hit ? b : b_hit;
+                b = bn;
+                W.t = hit ? W.t : tn;
+                W.k = k;
+                W.ix = hit ? W.ix : ix;
+                W.iy = hit ? W.iy : iy;
+                W.iz = hit ? W.iz : iz;
+                W.rx += cx && !hit ? W.sfx : (Real)0;
+                W.ry += cy && !hit ? W.sfy : (Real)0;
+                W.rz += cz && !hit ? W.sfz : (Real)0;
+                W.tx = W.rx * W.gx;
+                W.ty = W.ry * W.gy;
+                W.tz = W.rz * W.gz;
+                act = !(hit || away);
+                if (!act) state = hit ? BMC_HIT : (flight ? BMC_GONE : BMC_LIT);
+            }
         }
     }
     if (n_ev) {
         atomicAdd(&s_st[ST_EVENTS], (unsigned long long)n_ev);
         atomicAdd(&s_st[ST_LE], (unsigned long long)n_ev);
     }
-    if (vfree) atomicAdd(&s_st[ST_VFREE], (unsigned long long)vfree);
+    if (__lane_id() == 0 && vfree_w) atomicAdd(&s_st[ST_VFREE], (unsigned long long)vfree_w);
     __syncthreads();
     if (threadIdx.x < ST_N && s_st[threadIdx.x]) atomicAdd(&A.stats[threadIdx.x], s_st[threadIdx.x]);
 }
@@ -2196,12 +2439,17 @@ size_t render_dyn_lds(const KArgs<Real>& a, int mode) {
     return bytes;
 }
 
+// Ids a wavefront takes per fetch (see wave_fetch).
+static uint32_t fetch_block(int grid, int threads, uint64_t n) {
+    const uint64_t waves = (uint64_t)std::max(grid, 1) * (threads / WAVE);
+    return (uint32_t)std::min<uint64_t>(FETCH_BLOCK_MAX, std::max<uint64_t>(WAVE, n / (32 * waves)));
+}
+
 template <typename Real, int MODE, int TALLY, bool AIRZ = false, bool W32 = false, bool CAP = false>
 static hipError_t launch_r(const KArgs<Real>& a, int grid, hipStream_t s) {
     const size_t dyn = render_dyn_lds(a, MODE);
     KArgs<Real> b = a;
-    const uint64_t waves = (uint64_t)std::max(grid, 1) * (RenderThreads<MODE>::value / WAVE);
-    b.fetch_block = (uint32_t)std::min<uint64_t>(FETCH_BLOCK_MAX, std::max<uint64_t>(WAVE, a.n_photons / (32 * waves)));
+    b.fetch_block = fetch_block(grid, RenderThreads<MODE>::value, a.n_photons);
     hipLaunchKernelGGL((k_render<Real, MODE, TALLY, AIRZ, W32, CAP>), dim3(grid), dim3(RenderThreads<MODE>::value),
                        dyn, s, b);
     return hipGetLastError();
@@ -2261,7 +2509,9 @@ hipError_t launch_transport(const KArgs<Real>& a, int mode, int tally, int grid,
     }
     if (mode == MODE_VOXEL) return launch_r<Real, MODE_VOXEL, TALLY_F64>(a, grid, s);
     if (mode == MODE_BMC) {
-        hipLaunchKernelGGL(k_bmc<Real>, dim3(grid), dim3(BLOCK), 0, s, a);
+        KArgs<Real> b = a;
+        b.fetch_block = fetch_block(grid, BLOCK, (uint64_t)a.n_pix * a.n_pp);
+        hipLaunchKernelGGL(k_bmc<Real>, dim3(grid), dim3(BLOCK), 0, s, b);
         return hipGetLastError();
     }
     if (mode == MODE_MIXGRAD) {
