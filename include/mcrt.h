@@ -458,8 +458,9 @@ int mc_trace_paths(const mc_grid* grid, const void* beta, int n_cams, const mc_c
  * FP64 tallies (images as there) on at most max_waves wavefronts (a multiple
  * of 4; the launch may use fewer: *n_waves, host, gets the number), in which
  * wavefront w also stores, for its connection-walk steps first_step ..
- * first_step + n_steps - 1, the index into the library's copy of beta that
- * each of its 64 lanes asks for on that step (lanes with no ray, or in an
+ * first_step + n_steps - 1, the index (x fastest: the capture's copy of beta
+ * keeps that order, mc_render's runs along the cameras' view) that each of
+ * its 64 lanes asks for on that step (lanes with no ray, or in an
  * empty run of voxels, ask for index nx*ny*nz, which the walk's buffer
  * answers with zero and no memory access):
  * indices (device, max_waves * n_steps * 64 uint32) at

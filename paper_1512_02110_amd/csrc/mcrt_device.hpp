@@ -149,6 +149,9 @@ __device__ __forceinline__ void scatter_direction(Real& wx, Real& wy, Real& wz, 
 template <typename Real>
 struct DevGrid {
     int nx, ny, nz, nxy;
+    // index steps of a voxel on each axis in the library's copy of beta and its
+    // occupancy bitmask (elsewhere voxels are x fastest: 1, nx, nxy)
+    int lx, ly, lz;
     Real dx, dy, dz;     // voxel edges (km)
     Real idx, idy, idz;  // 1 / edge
     double ddx, ddy, ddz;  // voxel edges in double (the projection onto the cameras)

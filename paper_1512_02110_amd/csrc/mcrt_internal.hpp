@@ -220,10 +220,11 @@ hipError_t launch_normalize(double* img, const NormCam* cams, int n_cams, int64_
 hipError_t launch_grad_weights(double* gw, const double* dl, const NormCam* cams, int n_cams, int64_t n_pix,
                                double base, hipStream_t s);
 hipError_t launch_kahan_reduce(double* out, const float* pairs, int64_t n, hipStream_t s);
+// Copy of n_vox values in G's layout (lx, ly or lz = 1: that axis fastest, the others in x, y, z order).
 template <typename Real>
-hipError_t launch_build_mask(const KArgs<Real>& a, uint32_t* mask, hipStream_t s);
+hipError_t launch_layout(const Real* src, Real* dst, const DevGrid<Real>& G, hipStream_t s);
 template <typename Real>
-hipError_t launch_build_mask_aer(const KArgs<Real>& a, uint32_t* mask, hipStream_t s);
+hipError_t launch_build_mask(const KArgs<Real>& a, bool aer, uint32_t* mask, hipStream_t s);
 template <typename Real>
 hipError_t launch_air_column(const double* air, int64_t n_vox, int64_t nxy, int nz, Real* col, uint32_t* flag,
                              hipStream_t s);

@@ -192,13 +192,13 @@ __device__ __forceinline__ bool walk_begin(WalkRegs<Real>& W, const DevGrid<Real
     W.ix = ix;
     W.iy = iy;
     W.iz = iz;
-    W.k = ix + G.nx * iy + G.nxy * iz;
+    W.k = G.lx * ix + G.ly * iy + G.lz * iz;
     walk_axis(fx, wx, G.dx, W.sx, W.sfx, W.rx, W.gx, W.tx);
     walk_axis(fy, wy, G.dy, W.sy, W.sfy, W.ry, W.gy, W.ty);
     walk_axis(fz, wz, G.dz, W.sz, W.sfz, W.rz, W.gz, W.tz);
-    W.kx = W.sx;
-    W.ky = W.sy * G.nx;
-    W.kz = W.sz * G.nxy;
+    W.kx = W.sx * G.lx;
+    W.ky = W.sy * G.ly;
+    W.kz = W.sz * G.lz;
     W.t = (Real)0;
     const bool finite_f = fabs(fx) < (Real)4 && fabs(fy) < (Real)4 && fabs(fz) < (Real)4;
     return finite_f && (W.sx | W.sy | W.sz) != 0;
@@ -637,13 +637,14 @@ __device__ __forceinline__ void voxel_tally(const KArgs<Real>& A, JobQueue<Real,
 // the ray leaves the domain, so that the walk ends at its length and keeps
 // only the linear voxel index, not the voxel indices: the next crossing on
 // axis a is t_a = r_a g_a as in the free-flight walk (r_a counted from the
-// start voxel, t recomputed after every crossing), and a crossing that
-// rounding put just before the clipped end (so that k left the grid) ends
-// the walk too.
+// start voxel, t recomputed after every crossing), and a crossing out of a z
+// face or of the index range that rounding put just before the clipped end
+// ends the walk too (the z faces from rz, whatever the layout of the voxels).
 template <typename Real>
 struct ConnWalk {
     int k, kx, ky, kz;
     int iz, izs;  // layer of the current voxel and its step on a z crossing
+    Real rz_out;  // |rz| is above this once the walk has left through a z face
     Real sfx, sfy, sfz;
     Real rx, ry, rz;
     Real gx, gy, gz;
@@ -658,15 +659,16 @@ template <typename Real>
 __device__ __forceinline__ Real conn_begin(ConnWalk<Real>& C, const DevGrid<Real>& G, int ix, int iy, int iz, Real fx,
                                            Real fy, Real fz, Real wx, Real wy, Real wz) {
     int sx, sy, sz;
-    C.k = ix + G.nx * iy + G.nxy * iz;
+    C.k = G.lx * ix + G.ly * iy + G.lz * iz;
     walk_axis(fx, wx, G.dx, sx, C.sfx, C.rx, C.gx, C.tx);
     walk_axis(fy, wy, G.dy, sy, C.sfy, C.ry, C.gy, C.ty);
     walk_axis(fz, wz, G.dz, sz, C.sfz, C.rz, C.gz, C.tz);
-    C.kx = sx;
-    C.ky = sy * G.nx;
-    C.kz = sz * G.nxy;
+    C.kx = sx * G.lx;
+    C.ky = sy * G.ly;
+    C.kz = sz * G.lz;
     C.iz = iz;
     C.izs = sz;
+    C.rz_out = (Real)(sz > 0 ? G.nz - 1 - iz : iz) + fabs(C.rz) + (Real)0.5;
     C.t = (Real)0;
     // the domain face on each axis lies (n - 1 - i) voxels beyond the first
     // face when moving up, i voxels beyond it when moving down
@@ -767,7 +769,7 @@ __device__ __forceinline__ void job_step3(const WalkCtx<Real>& C, const uint32_t
     const bool cy = __builtin_amdgcn_inverse_ballot_w64(my);
     const bool cxy = __builtin_amdgcn_inverse_ballot_w64(mx | my);
     const u64 last = __builtin_amdgcn_ballot_w64(tn >= J.r);
-    const Real tend = fmin(tn, J.r);
+    const Real tend = __builtin_amdgcn_inverse_ballot_w64(last) ? J.r : tn;
     J.tau += (double)bo * (double)Lo;
     Ln = tend - W.t;
     W.t = tend;
@@ -780,9 +782,10 @@ __device__ __forceinline__ void job_step3(const WalkCtx<Real>& C, const uint32_t
     W.tx = W.rx * W.gx;
     W.ty = W.ry * W.gy;
     W.tz = W.rz * W.gz;
-    busy &= ~(last | __builtin_amdgcn_ballot_w64((uint32_t)W.k >= C.n_vox));
-    // (a lane that is done may be anywhere: the last voxel is a valid index to test)
-    const uint32_t kk = min((uint32_t)W.k, C.n_vox - 1u);
+    busy &= ~(last | __builtin_amdgcn_ballot_w64(fabs(W.rz) > W.rz_out) |
+              __builtin_amdgcn_ballot_w64((uint32_t)W.k >= C.n_vox));
+    // (a lane that is done may be anywhere: the zero word, which the bitmask covers)
+    const uint32_t kk = min((uint32_t)W.k, C.n_vox);
     const u64 occ = __builtin_amdgcn_ballot_w64(__builtin_amdgcn_ubfe(mask[kk >> msh5], kk >> C.msh, 1u) != 0u);
     if constexpr (AIRZ) {
         const uint32_t in = __builtin_amdgcn_inverse_ballot_w64(occ) ? kk : C.empty(W.iz);
@@ -1140,7 +1143,7 @@ __global__ void __launch_bounds__((RenderThreads<MODE>::value), (RenderWaves<Rea
             // frozen-event render: the estimate scaled by beta_le / beta at the collision
             Real fr = (Real)1;
             if (A.frozen && collided) {
-                const int64_t k = (int64_t)ph.ix + (int64_t)A.G.nx * ph.iy + (int64_t)A.G.nxy * ph.iz;
+                const int64_t k = (int64_t)A.G.lx * ph.ix + (int64_t)A.G.ly * ph.iy + (int64_t)A.G.lz * ph.iz;
                 fr = (Real)((double)A.beta_le[k] / (double)A.beta[k]);
             }
             for (int c = 0; c < A.n_cams; ++c) {
@@ -1332,7 +1335,8 @@ __global__ void __launch_bounds__(BLOCK) k_bin(KArgs<Real> A, int scatter) {
             if (A.mix_aer)  // the collision's score term: aerosol only, over the aerosol extinction
                 R.ab = R.ab != (Real)0 ? (Real)((double)R.a / __dmul_rn(A.mix_sig, A.mix_aer[k])) : (Real)0;
             else
-                R.ab = (Real)((double)R.a / (double)A.beta[k]);
+                R.ab = (Real)((double)R.a / (double)A.beta[(int64_t)A.G.lx * ix + (int64_t)A.G.ly * iy +
+                                                           (int64_t)A.G.lz * iz]);
         }
         for_each_tile(P, R, ix, iy, iz, vx, vy, vz, r, [&](int t) {
             if (t >= lo && t < hi) {
@@ -2410,39 +2414,63 @@ __global__ void k_grad_weights(double* gw, const double* dl, const NormCam* cams
     if (p < n_pix) gw[p] = dl[p] * pixel_norm(cams, n_cams, p, base);
 }
 
-// One 32-bit word of the occupancy bitmask per thread: bit j of word w is
-// set when a voxel of run 32 w + j has beta > 0 (or a non-finite beta,
-// which must reach the walk unchanged).
+// Copy of beta in the kernels' layout, for every outer index o the matrix
+// [slow][nx] of stride `row` transposed to [nx][slow] (slow = z: outer y; slow =
+// y: outer z), through LDS tiles so that both sides are coalesced.
 template <typename Real>
-__global__ void k_build_mask(KArgs<Real> A, uint32_t* mask) {
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= A.mask_words) return;
-    uint32_t word = 0;
-    for (int j = 0; j < 32; ++j) {
-        const int64_t k0 = ((int64_t)w * 32 + j) << A.msh;
-        const int64_t k1 = min(k0 + ((int64_t)1 << A.msh), A.n_vox);
-        bool any = false;
-        for (int64_t k = k0; k < k1 && !any; ++k) any = !(A.beta[k] == (Real)0) || !(A.beta_le[k] == (Real)0);
-        if (any) word |= 1u << j;
+__global__ void __launch_bounds__(BLOCK) k_transpose(const Real* src, Real* dst, int nx, int slow, int outer,
+                                                     int64_t row, int64_t plane) {
+    __shared__ Real s_t[32][33];
+    const int tx = (nx + 31) / 32, ts = (slow + 31) / 32;
+    const int64_t tiles = (int64_t)tx * ts * outer;
+    const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int x0 = (int)(t % tx) * 32, s0 = (int)((t / tx) % ts) * 32;
+        const int64_t o = t / ((int64_t)tx * ts);
+        for (int r = r0; r < 32; r += BLOCK / 32)
+            if (s0 + r < slow && x0 + c < nx) s_t[r][c] = src[x0 + c + row * (s0 + r) + plane * o];
+        __syncthreads();
+        for (int r = r0; r < 32; r += BLOCK / 32)
+            if (x0 + r < nx && s0 + c < slow) dst[s0 + c + (int64_t)slow * (x0 + r + (int64_t)nx * o)] = s_t[c][r];
+        __syncthreads();
     }
-    mask[w] = word;
 }
 
-// Occupancy mask of a mixture whose air depends on the height only: runs
-// holding aerosol (aer > 0); the air of the other voxels is the column's.
-template <typename Real>
-__global__ void k_build_mask_aer(KArgs<Real> A, uint32_t* mask) {
-    const int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= A.mask_words) return;
-    uint32_t word = 0;
-    for (int j = 0; j < 32; ++j) {
-        const int64_t k0 = ((int64_t)w * 32 + j) << A.msh;
-        const int64_t k1 = min(k0 + ((int64_t)1 << A.msh), A.n_vox);
+// The occupancy bitmask: bit j is set when a voxel of run j (2^msh consecutive
+// voxels of the library's copy) has beta > 0 (or a non-finite beta, which must
+// reach the walk unchanged), or with AER an aerosol value that is not zero (a
+// mixture whose air depends on the height only: the air of the other voxels is
+// the column's).  The last bit is the zero word's.  One wavefront per 64 runs:
+// it reads them in order, 64 voxels at a time, and lane l keeps run l's bit (a
+// thread per word, walking its 32 runs alone, took 419 us for 256 x 256 x 128
+// voxels and 21 us for 64^3).
+template <typename Real, bool AER>
+__global__ void __launch_bounds__(BLOCK) k_build_mask(KArgs<Real> A, uint32_t* mask) {
+    const uint32_t lane = __lane_id();
+    const int msh = A.msh;
+    const int64_t n_pair = (A.mask_words + 1) / 2;  // pairs of words
+    for (int64_t p = (int64_t)blockIdx.x * (BLOCK / WAVE) + threadIdx.x / WAVE; p < n_pair;
+         p += (int64_t)gridDim.x * (BLOCK / WAVE)) {
+        const int64_t k0 = (p * 64) << msh;
         bool any = false;
-        for (int64_t k = k0; k < k1 && !any; ++k) any = !(A.mix_aer[k] == 0.0);
-        if (any) word |= 1u << j;
+        for (int it = 0; it < 1 << msh; ++it) {
+            const int64_t k = k0 + (int64_t)it * 64 + lane;
+            bool on = false;
+            if (k < A.n_vox)
+                on = AER ? !(A.mix_aer[k] == 0.0) : !(A.beta[k] == (Real)0) || !(A.beta_le[k] == (Real)0);
+            const unsigned long long m = __ballot(on);
+            if (msh <= 6) {
+                // runs of 2^msh lanes: lane l's run is in this pass when l >> (6 - msh) == it
+                const int first = (int)((lane << msh) & 63u);
+                const unsigned long long run = msh == 6 ? ~0ull : (1ull << (1 << msh)) - 1ull;
+                if ((int)(lane >> (6 - msh)) == it) any = ((m >> first) & run) != 0ull;
+            } else if ((int)lane == it >> (msh - 6)) {
+                any = any || m != 0ull;
+            }
+        }
+        const unsigned long long bits = __ballot(any);
+        if (lane < 2u && 2 * p + lane < (int64_t)A.mask_words) mask[2 * p + lane] = (uint32_t)(bits >> (32u * lane));
     }
-    mask[w] = word;
 }
 
 // Air column of a mixture: col[iz] = the channel's extinction of an
@@ -2618,18 +2646,28 @@ template hipError_t launch_voxel_finish<double>(double*, const double*, int, con
                                                 hipStream_t);
 
 template <typename Real>
-hipError_t launch_build_mask(const KArgs<Real>& a, uint32_t* mask, hipStream_t s) {
-    hipLaunchKernelGGL(k_build_mask<Real>, dim3(blocks_for(a.mask_words)), dim3(BLOCK), 0, s, a, mask);
+hipError_t launch_layout(const Real* src, Real* dst, const DevGrid<Real>& G, hipStream_t s) {
+    if (G.lx == 1) return hipMemcpyAsync(dst, src, sizeof(Real) * (size_t)G.nxy * G.nz, hipMemcpyDeviceToDevice, s);
+    const bool z = G.lz == 1;
+    const int slow = z ? G.nz : G.ny, outer = z ? G.ny : G.nz;
+    const int64_t row = z ? G.nxy : G.nx, plane = z ? G.nx : G.nxy;
+    const int64_t tiles = (int64_t)((G.nx + 31) / 32) * ((slow + 31) / 32) * outer;
+    hipLaunchKernelGGL(k_transpose<Real>, dim3((unsigned)std::min<int64_t>(tiles, 65536)), dim3(BLOCK), 0, s, src, dst,
+                       G.nx, slow, outer, row, plane);
     return hipGetLastError();
 }
+template hipError_t launch_layout<float>(const float*, float*, const DevGrid<float>&, hipStream_t);
+template hipError_t launch_layout<double>(const double*, double*, const DevGrid<double>&, hipStream_t);
 
 template <typename Real>
-hipError_t launch_build_mask_aer(const KArgs<Real>& a, uint32_t* mask, hipStream_t s) {
-    hipLaunchKernelGGL(k_build_mask_aer<Real>, dim3(blocks_for(a.mask_words)), dim3(BLOCK), 0, s, a, mask);
+hipError_t launch_build_mask(const KArgs<Real>& a, bool aer, uint32_t* mask, hipStream_t s) {
+    const int grid = (a.mask_words / 2 + BLOCK / WAVE) / (BLOCK / WAVE);
+    if (aer)
+        hipLaunchKernelGGL((k_build_mask<Real, true>), dim3(grid), dim3(BLOCK), 0, s, a, mask);
+    else
+        hipLaunchKernelGGL((k_build_mask<Real, false>), dim3(grid), dim3(BLOCK), 0, s, a, mask);
     return hipGetLastError();
 }
-template hipError_t launch_build_mask_aer<float>(const KArgs<float>&, uint32_t*, hipStream_t);
-template hipError_t launch_build_mask_aer<double>(const KArgs<double>&, uint32_t*, hipStream_t);
 
 template <typename Real>
 hipError_t launch_air_column(const double* air, int64_t n_vox, int64_t nxy, int nz, Real* col, uint32_t* flag,
@@ -2682,8 +2720,8 @@ hipError_t launch_deposit(const KArgs<Real>& a, int tally, const DepositItem* it
 
 template hipError_t launch_deposit<float>(const KArgs<float>&, int, const DepositItem*, int, hipStream_t);
 template hipError_t launch_deposit<double>(const KArgs<double>&, int, const DepositItem*, int, hipStream_t);
-template hipError_t launch_build_mask<float>(const KArgs<float>&, uint32_t*, hipStream_t);
-template hipError_t launch_build_mask<double>(const KArgs<double>&, uint32_t*, hipStream_t);
+template hipError_t launch_build_mask<float>(const KArgs<float>&, bool, uint32_t*, hipStream_t);
+template hipError_t launch_build_mask<double>(const KArgs<double>&, bool, uint32_t*, hipStream_t);
 template hipError_t launch_write_cams<float>(const CamChunk&, DevCam<float>*, NormCam*, hipStream_t);
 template hipError_t launch_write_cams<double>(const CamChunk&, DevCam<double>*, NormCam*, hipStream_t);
 template <typename Real>
