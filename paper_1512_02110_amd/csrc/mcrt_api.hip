@@ -821,7 +821,12 @@ int run_tape(KArgs<Real> A, int tally, uint64_t n_photons, uint64_t pid0, int64_
     if (max_blocks < 1 || P - r_min < 64) return TAPE_FALLBACK;
     max_nw = max_blocks * wpb;
     h_wave.resize(max_nw);
-    r_cap = P / 2;
+    // (a workload measured before: split so that its rays and its bins, four
+    // and a half crossings per ray, fill together; in halves the bins of the
+    // whole call do not fit a space sized for it, and every call took two
+    // chunks, each with its own tails)
+    r_cap = hint > 0.0 ? (uint64_t)((double)P * (1.25 / (1.25 + 4.5))) : P / 2;
+    r_cap = std::min(std::max(r_cap, r_min), P - r_min);
 
     if (t_transport) {
         CHECK_HIP(hipEventCreate(&r0));
@@ -1632,7 +1637,7 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
                 CHECK_HIP(available_bytes(&avail));
                 mp.max_chunk = std::min<uint64_t>(std::min<uint64_t>(prm->n_photons, (uint64_t)1 << 22),
                                                   avail / 8 / row);
-                CHECK_HIP(transport_occupancy<Real>(A, MODE_MIXGRAD, tally, &per_mix));
+                CHECK_HIP(mix_path_occupancy<Real>(&per_mix));
                 mp.grid = (int)std::min<uint64_t>((mp.max_chunk + BLOCK - 1) / BLOCK,
                                                   (uint64_t)n_cu * (per_mix > 0 ? per_mix : 1));
                 if (mp.max_chunk == 0 || lib_alloc((void**)&mix_rows, row * mp.max_chunk, stream) != hipSuccess) {

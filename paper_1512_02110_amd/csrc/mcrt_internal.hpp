@@ -231,6 +231,8 @@ hipError_t launch_air_column(const double* air, int64_t n_vox, int64_t nxy, int 
 template <typename Real>
 hipError_t launch_mix_path(const KArgs<Real>& a, int grid, hipStream_t s);
 template <typename Real>
+hipError_t mix_path_occupancy(int* blocks_per_cu);
+template <typename Real>
 hipError_t launch_mix_total(Real* beta, const double* air, const double* aer, double sig, int64_t n, int64_t pad,
                             hipStream_t s);
 template <typename Real>
