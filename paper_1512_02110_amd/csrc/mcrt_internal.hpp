@@ -172,9 +172,9 @@ constexpr int TILE_VOX = 16384;   // voxels of a gradient tile
 // rounding carries across the tile's x or y face lands in a padding slot,
 // which is never flushed, instead of in another voxel of the tile.
 constexpr int TILE_LDS = 18560;
-constexpr int MAX_TAPE_TILES = 8192;  // per-tile counters of the binning pass: up to 104 KB of LDS
+constexpr int MAX_TAPE_TILES = 8192;  // per-tile counters of the binning pass: up to 52 KB of LDS
 constexpr int BIN_LDS_CAMS = 2048;    // camera pixel offsets the binning pass keeps in LDS
-constexpr int BIN_GROUP_TILES = 4096; // tiles per scatter pass (3 LDS words each)
+constexpr int BIN_GROUP_TILES = 4096; // tiles per scatter pass (2 LDS words each)
 // Binning blocks of a pass: at least BIN_BLOCKS_PER_CU per compute unit
 // (a slice of the ray tape split over up to BIN_SPLIT_MAX blocks): a pass of
 // a few hundred wavefront slices would otherwise fill a fraction of the GPU,

@@ -1271,154 +1271,252 @@ __global__ void __launch_bounds__((RenderThreads<MODE>::value), (RenderWaves<Rea
 // ---------------------------------------------------------------------------
 // Binning of the ray tape by gradient tile.
 
-// Ray of a tape record going to camera c: start voxel, unit direction to the
-// camera and length, recomputed as the local estimate formed them.  False
-// for a record outside the grid or the camera table.
+// Camera centre in voxel units (integer and fraction), as the binning and the
+// deposit keep it in LDS.
 template <typename Real>
-__device__ __forceinline__ bool tape_ray(const KArgs<Real>& A, const TapeRec<Real>& R, uint32_t c, int& ix, int& iy,
-                                         int& iz, Real& vx, Real& vy, Real& vz, Real& r) {
+struct alignas(16) CamCentre {
+    int ix, iy, iz;
+    Real fx, fy, fz;
+};
+
+template <typename Real>
+__device__ __forceinline__ CamCentre<Real> cam_centre(const DevCam<Real>& cam) {
+    CamCentre<Real> cc;
+    cc.ix = cam.icx;
+    cc.iy = cam.icy;
+    cc.iz = cam.icz;
+    cc.fx = cam.fcx;
+    cc.fy = cam.fcy;
+    cc.fz = cam.fcz;
+    return cc;
+}
+
+// Ray of a tape record going to a camera: start voxel, unit direction to the
+// camera and length, recomputed as the local estimate formed them.  False
+// for a record outside the grid.
+template <typename Real>
+__device__ __forceinline__ bool tape_ray(const KArgs<Real>& A, const CamCentre<Real>& cam, const TapeRec<Real>& R, int& ix,
+                                         int& iy, int& iz, Real& vx, Real& vy, Real& vz, Real& r) {
     ix = (int)(R.vox & 2047u);
     iy = (int)((R.vox >> 11) & 2047u);
     iz = (int)(R.vox >> 22);
-    if (ix >= A.G.nx || iy >= A.G.ny || iz >= A.G.nz || c >= (uint32_t)A.n_cams) return false;
-    const DevCam<Real>& cam = A.cams[c];
-    const Real dx = ((Real)(ix - cam.icx) + (R.fx - cam.fcx)) * A.G.dx;
-    const Real dy = ((Real)(iy - cam.icy) + (R.fy - cam.fcy)) * A.G.dy;
-    const Real dz = ((Real)(iz - cam.icz) + (R.fz - cam.fcz)) * A.G.dz;
+    const Real dx = ((Real)(ix - cam.ix) + (R.fx - cam.fx)) * A.G.dx;
+    const Real dy = ((Real)(iy - cam.iy) + (R.fy - cam.fy)) * A.G.dy;
+    const Real dz = ((Real)(iz - cam.iz) + (R.fz - cam.fz)) * A.G.dz;
     r = m_sqrt(dx * dx + dy * dy + dz * dz);
     const Real ir = (Real)1 / r;
     vx = -dx * ir;
     vy = -dy * ir;
     vz = -dz * ir;
-    return true;
-}
-
-// Calls f(tile) for every tile the ray crosses, in order (a walk over the
-// grid of tiles; a ray without a usable direction only has its start tile).
-template <typename Real, typename F>
-__device__ __forceinline__ void for_each_tile(const Tape<Real>& P, const TapeRec<Real>& R, int ix, int iy, int iz,
-                                              Real vx, Real vy, Real vz, Real r, F&& f) {
-    WalkRegs<Real> W;
-    const int tix = ix >> P.shx, tiy = iy >> P.shy, tiz = iz >> P.shz;
-    const Real ftx = ((Real)(ix & ((1 << P.shx) - 1)) + R.fx) * P.itx;
-    const Real fty = ((Real)(iy & ((1 << P.shy) - 1)) + R.fy) * P.ity;
-    const Real ftz = ((Real)(iz & ((1 << P.shz) - 1)) + R.fz) * P.itz;
-    if (!walk_begin(W, P.T, tix, tiy, tiz, ftx, fty, ftz, vx, vy, vz)) {
-        f(tix + P.T.nx * tiy + P.T.nxy * tiz);
-        return;
-    }
-    for (;;) {
-        f(W.k);
-        bool cx, cy, cz;
-        const Real tn = walk_next(W, cx, cy, cz);
-        if (tn >= r || walk_cross(W, P.T, tn, cx, cy, cz)) return;
-    }
+    return ix < A.G.nx && iy < A.G.ny && iz < A.G.nz;
 }
 
 // Camera of global pixel p: the last camera whose first pixel is <= p
-// (binary search over the cameras' first pixels: in LDS for the first
-// BIN_LDS_CAMS cameras, else in the device table).
+// (bisection over the cameras' first pixels: in LDS, or in the device table
+// when there are more than BIN_LDS_CAMS cameras).  `top` is the largest power
+// of two below n_cams (0 for one camera).
 template <typename Real>
-__device__ __forceinline__ uint32_t camera_of(const KArgs<Real>& A, const int32_t* s_off, uint32_t p) {
-    int lo = 0, hi = A.n_cams - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        const int32_t off = mid < BIN_LDS_CAMS ? s_off[mid] : A.cams[mid].pix_off;
-        if ((uint32_t)off <= p) lo = mid;
-        else hi = mid - 1;
+__device__ __forceinline__ uint32_t camera_of(const KArgs<Real>& A, const int32_t* s_off, int top, uint32_t p) {
+    int c = 0;
+    if (A.n_cams <= BIN_LDS_CAMS) {
+        for (int d = top; d > 0; d >>= 1) {
+            const int m = c + d;
+            const int off = s_off[min(m, A.n_cams - 1)];
+            c = (m < A.n_cams) & ((uint32_t)off <= p) ? m : c;
+        }
+    } else {
+        for (int d = top; d > 0; d >>= 1) {
+            const int m = c + d;
+            const int off = A.cams[min(m, A.n_cams - 1)].pix_off;
+            c = (m < A.n_cams) & ((uint32_t)off <= p) ? m : c;
+        }
     }
-    return (uint32_t)lo;
+    return (uint32_t)c;
 }
 
-// Every ray of the block's part of its wavefront slice (part
-// blockIdx.x % split of slice w0 + blockIdx.x / split): f(record with its
-// weight and camera index, start voxel, direction, length).  A tape of local
-// estimates (scale_gw) takes the weight gw[pixel] * a here; rays of zero
-// weight are skipped.
-template <typename Real, typename F>
-__device__ __forceinline__ void for_each_block_ray(const KArgs<Real>& A, const int32_t* s_off, F&& f) {
+__device__ __forceinline__ uint32_t swap_pair(uint32_t v) {  // the value of lane ^ 1
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true);
+}
+
+// A record as 16-byte parts, and the stores of a wavefront's records R to bin
+// slots (put: this lane stores one).  An FP32 record is two parts: lanes 2i
+// and 2i + 1 exchange parts once per ray (begin), so that one store
+// instruction writes the whole 32 bytes of lane 2i's record and the next those
+// of lane 2i + 1's: half as many cache lines per instruction as with a part of
+// every lane's record in each.
+template <typename Real>
+struct BinStore {
+    static constexpr bool PAIR = sizeof(TapeRec<Real>) == 32;
+    static constexpr int PARTS = (int)(sizeof(TapeRec<Real>) / 16);
+    uint4 part[PARTS];
+
+    __device__ __forceinline__ void begin(const TapeRec<Real>& R) {
+        __builtin_memcpy(part, &R, sizeof(R));
+        if constexpr (PAIR) {
+            const bool odd = __lane_id() & 1u;
+            exchange(part[0].x, part[1].x, odd);
+            exchange(part[0].y, part[1].y, odd);
+            exchange(part[0].z, part[1].z, odd);
+            exchange(part[0].w, part[1].w, odd);
+        }
+    }
+    // even lanes send their b for the odd neighbour's a, and the other way round
+    static __device__ __forceinline__ void exchange(uint32_t& a, uint32_t& b, bool odd) {
+        const uint32_t got = swap_pair(odd ? a : b);
+        a = odd ? got : a;
+        b = odd ? b : got;
+    }
+    // (the whole wavefront calls this)
+    __device__ __forceinline__ void store(TapeRec<Real>* bins, uint32_t slot, bool put) const {
+        uint4* q = reinterpret_cast<uint4*>(bins);
+        if constexpr (PAIR) {
+            const uint32_t odd = __lane_id() & 1u;
+            const uint32_t other = swap_pair(slot);
+            const bool oput = swap_pair(put ? 1u : 0u) != 0u;
+            if (odd ? oput : put) q[(size_t)2 * (odd ? other : slot) + odd] = part[0];
+            if (odd ? put : oput) q[(size_t)2 * (odd ? slot : other) + odd] = part[1];
+        } else if (put) {
+            for (int i = 0; i < PARTS; ++i) q[(size_t)PARTS * slot + i] = part[i];
+        }
+    }
+};
+
+// Dynamic LDS of the binning passes: the camera centres (CAMS_LDS), the
+// cameras' first pixels, a counter per tile of the pass and for the scatter
+// the end of the block's slots in each.
+template <typename Real>
+size_t bin_lds_bytes(int n_cams, bool cams_lds, bool scatter, size_t tiles) {
+    return (cams_lds ? sizeof(CamCentre<Real>) * (size_t)n_cams : 0) +
+           sizeof(uint32_t) * ((size_t)min(n_cams, BIN_LDS_CAMS) + (scatter ? 2 : 1) * tiles);
+}
+
+// Block b bins part b % split of wavefront slice w0 + b / split of the rays.
+//
+// Count pass: for every tile t, the records of the block's rays in t go to
+// slice[t][block] and are added to tile_count[t].
+// Scatter pass, after the scan: every ray, with its camera in place of its
+// pixel, is copied into the bin of every tile in [t_lo, t_hi) it crosses, at
+// the block's slots from slice[t][block] on.  Both passes run the same code,
+// so they find the same tiles; should they ever disagree, a block only fills
+// its own slots (extra records are dropped, unfilled slots get empty records
+// with a = 0), so every bin slot holds valid data.
+//
+// A tape of local estimates (scale_gw) takes the weight gw[pixel] * a here;
+// rays of zero weight are skipped.
+//
+// The wavefront's 64 rays step through their tiles together (a walk over the
+// grid of tiles; a ray without a usable direction only has its start tile).
+// For 8e7 rays on 64^3 (2.4e8 records in 16 tiles) the count takes 0.84 ms and
+// the scatter 3.4 ms, in which it writes 7.9 GB.  A search of the cameras
+// through a pointer to LDS or to the table, centres read from the table, a
+// record stored by its own lane and the next ray fetched only when it is
+// needed took 1.02 and 4.4 ms.
+template <typename Real, bool SCATTER, bool CAMS_LDS>
+__global__ void __launch_bounds__(BLOCK) k_bin(KArgs<Real> A) {
+    extern __shared__ __align__(16) unsigned char s_raw[];
     const Tape<Real>& P = A.tp;
+    const int lo = SCATTER ? P.t_lo : 0, hi = SCATTER ? P.t_hi : P.n_tiles;
+    const int n_off = min(A.n_cams, BIN_LDS_CAMS);
+    const int b = blockIdx.x;
+    CamCentre<Real>* s_cam = reinterpret_cast<CamCentre<Real>*>(s_raw);
+    int32_t* s_off = reinterpret_cast<int32_t*>(s_raw + (CAMS_LDS ? sizeof(CamCentre<Real>) * A.n_cams : 0));
+    uint32_t* s_cur = reinterpret_cast<uint32_t*>(s_off + n_off);  // the next slot (count: the records so far)
+    uint32_t* s_end = s_cur + (hi - lo);
+    for (int i = threadIdx.x; i < hi - lo; i += BLOCK) {
+        if constexpr (SCATTER) {
+            const size_t row = (size_t)(lo + i) * P.n_slices;
+            const uint32_t first = P.slice[row + b];
+            const uint32_t next = b + 1 < P.n_slices ? P.slice[row + b + 1] : P.tile_end[lo + i];
+            s_cur[i] = first;
+            s_end[i] = max(first, next);
+        } else {
+            s_cur[i] = 0u;
+        }
+    }
+    for (int i = threadIdx.x; i < n_off; i += BLOCK) s_off[i] = A.cams[i].pix_off;
+    if constexpr (CAMS_LDS)
+        for (int i = threadIdx.x; i < A.n_cams; i += BLOCK) s_cam[i] = cam_centre(A.cams[i]);
+    __syncthreads();
+
     const uint32_t split = (uint32_t)P.split;
     const size_t w = (size_t)P.w0 + blockIdx.x / split;
     const uint64_t n = min(P.wave_count[w], P.rw), part = blockIdx.x % split;
     const uint32_t j0 = (uint32_t)(n * part / split), j1 = (uint32_t)(n * (part + 1) / split);
-    for (uint32_t j = j0 + threadIdx.x; j < j1; j += BLOCK) {
-        TapeRec<Real> R = P.rec[w * P.rw + j];
-        if (P.scale_gw) R.a = (Real)((R.id < (uint32_t)A.n_pix ? A.gw[R.id] : 0.0) * (double)R.a);
-        if (R.a == (Real)0) continue;
-        R.id = camera_of(A, s_off, R.id);
-        int ix, iy, iz;
-        Real vx, vy, vz, r;
-        if (tape_ray(A, R, R.id, ix, iy, iz, vx, vy, vz, r)) f(R, ix, iy, iz, vx, vy, vz, r);
-    }
-}
-
-// Count pass (scatter = 0): for every tile t, the records of the block's
-// rays in t go to slice[t][block] and are added to tile_count[t].
-// Scatter pass (scatter = 1), after the scan: every ray, with its camera in
-// place of its pixel, is copied into the bin of every tile in [t_lo, t_hi)
-// it crosses, at the block's slots from slice[t][block] on.  Both passes run
-// the same code, so they find the same tiles; should they ever disagree, a
-// block only fills its own slots (extra records are dropped, unfilled slots
-// get empty records with a = 0), so every bin slot holds valid data.
-//
-// Dynamic LDS: the first pixels of the cameras (bin_cams words), then one
-// counter per tile of the pass, and for the scatter two more per tile.
-template <typename Real>
-__global__ void __launch_bounds__(BLOCK) k_bin(KArgs<Real> A, int scatter) {
-    extern __shared__ uint32_t s_bin[];
-    const Tape<Real>& P = A.tp;
-    const int lo = scatter ? P.t_lo : 0, hi = scatter ? P.t_hi : P.n_tiles;
-    const int n_off = min(A.n_cams, BIN_LDS_CAMS);
-    const int b = blockIdx.x;
-    int32_t* s_off = reinterpret_cast<int32_t*>(s_bin);
-    uint32_t* s_cnt = s_bin + n_off;
-    uint32_t* s_base = s_cnt + (hi - lo);
-    uint32_t* s_lim = s_base + (hi - lo);
-    for (int i = threadIdx.x; i < hi - lo; i += BLOCK) {
-        s_cnt[i] = 0u;
-        if (scatter) {
-            const size_t row = (size_t)(lo + i) * P.n_slices;
-            const uint32_t first = P.slice[row + b];
-            const uint32_t next = b + 1 < P.n_slices ? P.slice[row + b + 1] : P.tile_end[lo + i];
-            s_base[i] = first;
-            s_lim[i] = next > first ? next - first : 0u;
-        }
-    }
-    for (int i = threadIdx.x; i < n_off; i += BLOCK) s_off[i] = A.cams[i].pix_off;
-    __syncthreads();
-    for_each_block_ray(A, s_off, [&](const TapeRec<Real>& R0, int ix, int iy, int iz, Real vx, Real vy, Real vz, Real r) {
-        TapeRec<Real> R = R0;
-        if (scatter) {
-            const int64_t k = ix + A.G.nx * iy + A.G.nxy * iz;
+    const TapeRec<Real>* rec = P.rec + w * P.rw;
+    const int top = A.n_cams > 1 ? 1 << (31 - __clz(A.n_cams - 1)) : 0;
+    uint32_t j = j0 + threadIdx.x;
+    TapeRec<Real> nxt;
+    nxt.vox = nxt.id = 0u;
+    nxt.fx = nxt.fy = nxt.fz = nxt.a = nxt.ab = (Real)0;
+    if (j < j1) nxt = rec[j];
+    for (uint32_t jw = j0 + (threadIdx.x & ~63u); jw < j1; jw += BLOCK, j += BLOCK) {
+        TapeRec<Real> R = nxt;
+        bool on = j < j1;
+        // this ray's fetches, then the next ray's
+        const uint32_t pix = R.id;
+        double gw = 1.0;
+        if (P.scale_gw) gw = pix < (uint32_t)A.n_pix ? A.gw[pix] : 0.0;
+        int ix = (int)(R.vox & 2047u), iy = (int)((R.vox >> 11) & 2047u), iz = (int)(R.vox >> 22);
+        on = on && ix < A.G.nx && iy < A.G.ny && iz < A.G.nz;
+        double bk = 1.0;
+        if (SCATTER && on) {
             if (A.mix_aer)  // the collision's score term: aerosol only, over the aerosol extinction
-                R.ab = R.ab != (Real)0 ? (Real)((double)R.a / __dmul_rn(A.mix_sig, A.mix_aer[k])) : (Real)0;
+                bk = __dmul_rn(A.mix_sig, A.mix_aer[(int64_t)ix + (int64_t)A.G.nx * iy + (int64_t)A.G.nxy * iz]);
             else
-                R.ab = (Real)((double)R.a / (double)A.beta[(int64_t)A.G.lx * ix + (int64_t)A.G.ly * iy +
-                                                           (int64_t)A.G.lz * iz]);
+                bk = (double)A.beta[(int64_t)A.G.lx * ix + (int64_t)A.G.ly * iy + (int64_t)A.G.lz * iz];
         }
-        for_each_tile(P, R, ix, iy, iz, vx, vy, vz, r, [&](int t) {
-            if (t >= lo && t < hi) {
-                const uint32_t p = atomicAdd(&s_cnt[t - lo], 1u);
-                if (scatter && p < s_lim[t - lo]) P.brec[s_base[t - lo] + p] = R;
+        if (j + BLOCK < j1) nxt = rec[j + BLOCK];
+        R.id = camera_of(A, s_off, top, pix);
+        if (P.scale_gw) R.a = (Real)(gw * (double)R.a);
+        on = on && R.a != (Real)0;
+        CamCentre<Real> cc;
+        if constexpr (CAMS_LDS) cc = s_cam[R.id];
+        else cc = cam_centre(A.cams[R.id]);
+        Real vx, vy, vz, r;
+        tape_ray(A, cc, R, ix, iy, iz, vx, vy, vz, r);
+        if (SCATTER) R.ab = A.mix_aer && R.ab == (Real)0 ? (Real)0 : (Real)((double)R.a / bk);
+        BinStore<Real> S;
+        if constexpr (SCATTER) S.begin(R);
+        WalkRegs<Real> W;
+        const int tix = ix >> P.shx, tiy = iy >> P.shy, tiz = iz >> P.shz;
+        const Real ftx = ((Real)(ix & ((1 << P.shx) - 1)) + R.fx) * P.itx;
+        const Real fty = ((Real)(iy & ((1 << P.shy) - 1)) + R.fy) * P.ity;
+        const Real ftz = ((Real)(iz & ((1 << P.shz) - 1)) + R.fz) * P.itz;
+        const bool walks = walk_begin(W, P.T, tix, tiy, tiz, ftx, fty, ftz, vx, vy, vz);
+        while (__builtin_amdgcn_ballot_w64(on)) {
+            const int i = W.k - lo;
+            const bool in = on && (unsigned)i < (unsigned)(hi - lo);
+            if constexpr (SCATTER) {
+                uint32_t slot = 0u;
+                bool put = false;
+                if (in) {
+                    slot = atomicAdd(&s_cur[i], 1u);
+                    put = slot < s_end[i];
+                }
+                S.store(P.brec, slot, put);
+            } else if (in) {
+                atomicAdd(&s_cur[i], 1u);
             }
-        });
-    });
-    __syncthreads();
-    if (!scatter) {
-        for (int i = threadIdx.x; i < hi - lo; i += BLOCK) {
-            const uint32_t n = s_cnt[i];
-            P.slice[(size_t)(lo + i) * P.n_slices + b] = n;
-            if (n) atomicAdd(&P.tile_count[lo + i], n);
+            bool cx, cy, cz;
+            const Real tn = walk_next(W, cx, cy, cz);
+            on = on && walks && !(tn >= r) && !walk_cross(W, P.T, tn, cx, cy, cz);
         }
-        return;
     }
-    TapeRec<Real> E;
-    E.vox = 0u;
-    E.id = 0u;
-    E.fx = E.fy = E.fz = E.a = E.ab = (Real)0;
-    for (int i = 0; i < hi - lo; ++i)
-        for (uint32_t p = s_cnt[i] + threadIdx.x; p < s_lim[i]; p += BLOCK) P.brec[s_base[i] + p] = E;
+    __syncthreads();
+    if constexpr (!SCATTER) {
+        for (int i = threadIdx.x; i < hi - lo; i += BLOCK) {
+            const uint32_t c = s_cur[i];
+            P.slice[(size_t)(lo + i) * P.n_slices + b] = c;
+            if (c) atomicAdd(&P.tile_count[lo + i], c);
+        }
+    } else {
+        TapeRec<Real> E;
+        E.vox = 0u;
+        E.id = 0u;
+        E.fx = E.fy = E.fz = E.a = E.ab = (Real)0;
+        for (int i = 0; i < hi - lo; ++i)
+            for (uint32_t p = s_cur[i] + threadIdx.x; p < s_end[i]; p += BLOCK) P.brec[p] = E;
+    }
 }
 
 // Scan of the count pass: for each tile t of [t_lo, t_hi) (one block per
@@ -1472,14 +1570,6 @@ struct DepWalk {
     Real t, len;
 };
 
-// Camera centre in voxel units (integer and fraction), as the deposit keeps
-// it in LDS.
-template <typename Real>
-struct alignas(16) CamCentre {
-    int ix, iy, iz;
-    Real fx, fy, fz;
-};
-
 // Start the deposit of binned record R: a / beta(k_e) if the ray starts in
 // the tile, then the walk of the part of the ray inside the tile (false
 // when the record is empty or that part has no length).  Straight-line code
@@ -1496,18 +1586,7 @@ __device__ __forceinline__ bool deposit_begin(const KArgs<Real>& A, const DevGri
     const uint32_t c = ok ? R.id : 0u;  // keeps the camera read in bounds
     // all cameras in LDS, or all read from global memory: one kind of load
     // (a choice per lane would become a generic-address load)
-    CamCentre<Real> cc;
-    if (CAMS_LDS) {
-        cc = s_cam[c];
-    } else {
-        const DevCam<Real>& cam = A.cams[c];
-        cc.ix = cam.icx;
-        cc.iy = cam.icy;
-        cc.iz = cam.icz;
-        cc.fx = cam.fcx;
-        cc.fy = cam.fcy;
-        cc.fz = cam.fcz;
-    }
+    const CamCentre<Real> cc = CAMS_LDS ? s_cam[c] : cam_centre(A.cams[c]);
     // direction and length to the camera, as the local estimate formed them
     const Real dx = ((Real)(i0x - cc.ix) + (R.fx - cc.fx)) * A.G.dx;
     const Real dy = ((Real)(i0y - cc.iy) + (R.fy - cc.fy)) * A.G.dy;
@@ -1612,17 +1691,7 @@ __global__ void __launch_bounds__(DEPOSIT_BLOCK) k_deposit(KArgs<Real> A, const 
     const int nloc = pxy * L.nz;
     const uint32_t nloc_b = (uint32_t)(sizeof(double) * nloc);
     for (int i = threadIdx.x; i < nloc; i += DEPOSIT_BLOCK) s_g[i] = 0.0;
-    for (int i = threadIdx.x; CAMS_LDS && i < A.n_cams; i += DEPOSIT_BLOCK) {
-        const DevCam<Real>& cam = A.cams[i];
-        CamCentre<Real> cc;
-        cc.ix = cam.icx;
-        cc.iy = cam.icy;
-        cc.iz = cam.icz;
-        cc.fx = cam.fcx;
-        cc.fy = cam.fcy;
-        cc.fz = cam.fcz;
-        s_cam[i] = cc;
-    }
+    for (int i = threadIdx.x; CAMS_LDS && i < A.n_cams; i += DEPOSIT_BLOCK) s_cam[i] = cam_centre(A.cams[i]);
     // every slot of the tile's bin holds a record (or an empty one)
     const uint32_t hi = it.hi;
     if (threadIdx.x == 0) s_next = it.lo;
@@ -2897,8 +2966,16 @@ hipError_t launch_bin(const KArgs<Real>& a, bool scatter, hipStream_t s) {
     const int grid = a.tp.n_slices;  // split blocks per wavefront slice
     if (grid <= 0) return hipSuccess;
     const size_t tiles = scatter ? (size_t)(a.tp.t_hi - a.tp.t_lo) : (size_t)a.tp.n_tiles;
-    const size_t dyn = sizeof(uint32_t) * ((size_t)std::min(a.n_cams, BIN_LDS_CAMS) + (scatter ? 3 : 1) * tiles);
-    hipLaunchKernelGGL(k_bin<Real>, dim3(grid), dim3(BLOCK), dyn, s, a, scatter ? 1 : 0);
+    const bool lds = a.n_cams <= DEP_LDS_CAMS;
+    const size_t dyn = bin_lds_bytes<Real>(a.n_cams, lds, scatter, tiles);
+    if (scatter && lds)
+        hipLaunchKernelGGL((k_bin<Real, true, true>), dim3(grid), dim3(BLOCK), dyn, s, a);
+    else if (scatter)
+        hipLaunchKernelGGL((k_bin<Real, true, false>), dim3(grid), dim3(BLOCK), dyn, s, a);
+    else if (lds)
+        hipLaunchKernelGGL((k_bin<Real, false, true>), dim3(grid), dim3(BLOCK), dyn, s, a);
+    else
+        hipLaunchKernelGGL((k_bin<Real, false, false>), dim3(grid), dim3(BLOCK), dyn, s, a);
     return hipGetLastError();
 }
 
