@@ -75,45 +75,58 @@ struct Box {
     int x0, y0, z0, x1, y1, z1;  // voxels [x0, x1) x ...
 };
 
-// Voxels of the segment p + t v, t in [0, tmax] (v unit), that lie in the
-// box, in order: f(linear index, length inside), with IJK f(linear index, ix,
-// iy, iz, length inside).  The segment is clipped to the box first; ties between axes go to the
-// lowest axis.  Every choice between axes is a select of plain registers: the
-// state as arrays indexed by the axis lives in scratch memory, and with it and
-// a division per crossing the transmittances of 127 x 90 x 77 voxels to 16
-// cameras took 5.2 ms.  Instruction bound: about 25 a step.
-template <bool IJK, typename F>
-__device__ __forceinline__ void seg_walk(const VoxArgs& A, const Box& b, double px, double py, double pz, double vx,
-                                         double vy, double vz, double tmax, F&& f) {
-    const double ivx = 1.0 / vx, ivy = 1.0 / vy, ivz = 1.0 / vz;
-    double t0 = 0.0, t1 = tmax;
-    if (!axis_clip(px, vx, ivx, A.dx, b.x0, b.x1, t0, t1)) return;
-    if (!axis_clip(py, vy, ivy, A.dy, b.y0, b.y1, t0, t1)) return;
-    if (!axis_clip(pz, vz, ivz, A.dz, b.z0, b.z1, t0, t1)) return;
-    if (!(t1 > t0)) return;
+// The voxels of a segment p + t v, t in [0, tmax] (v unit), that lie in a box,
+// in order.  The segment is clipped to the box first; ties between axes go to
+// the lowest axis.  Every choice between axes is a select of plain registers:
+// the state as arrays indexed by the axis lives in scratch memory, and with it
+// and a division per crossing the transmittances of 127 x 90 x 77 voxels to 16
+// cameras took 5.2 ms.  About 25 instructions a step.
+struct SegWalk {
     WalkAxis64 X, Y, Z;
-    axis_begin(X, px, vx, ivx, A.dx, t0, b.x0, b.x1, t1);
-    axis_begin(Y, py, vy, ivy, A.dy, t0, b.y0, b.y1, t1);
-    axis_begin(Z, pz, vz, ivz, A.dz, t0, b.z0, b.z1, t1);
-    const int nxy = A.nx * A.ny;
-    int k = X.i + A.nx * Y.i + nxy * Z.i;
-    int ix = X.i, iy = Y.i, iz = Z.i;
-    const int kx = X.s, ky = Y.s * A.nx, kz = Z.s * nxy;
-    double t = t0, tx = X.t0, ty = Y.t0, tz = Z.t0;
-    for (;;) {
+    double t, t1, tx, ty, tz;
+    int k, kx, ky, kz;
+
+    // false: no voxel
+    __device__ __forceinline__ bool begin(const VoxArgs& A, const Box& b, double px, double py, double pz, double vx,
+                                          double vy, double vz, double tmax) {
+        const double ivx = 1.0 / vx, ivy = 1.0 / vy, ivz = 1.0 / vz;
+        double t0 = 0.0;
+        t1 = tmax;
+        if (!axis_clip(px, vx, ivx, A.dx, b.x0, b.x1, t0, t1)) return false;
+        if (!axis_clip(py, vy, ivy, A.dy, b.y0, b.y1, t0, t1)) return false;
+        if (!axis_clip(pz, vz, ivz, A.dz, b.z0, b.z1, t0, t1)) return false;
+        if (!(t1 > t0)) return false;
+        axis_begin(X, px, vx, ivx, A.dx, t0, b.x0, b.x1, t1);
+        axis_begin(Y, py, vy, ivy, A.dy, t0, b.y0, b.y1, t1);
+        axis_begin(Z, pz, vz, ivz, A.dz, t0, b.z0, b.z1, t1);
+        const int nxy = A.nx * A.ny;
+        k = X.i + A.nx * Y.i + nxy * Z.i;
+        kx = X.s;
+        ky = Y.s * A.nx;
+        kz = Z.s * nxy;
+        t = t0;
+        tx = X.t0;
+        ty = Y.t0;
+        tz = Z.t0;
+        return true;
+    }
+    // The length in voxel k, then k moves on; false when it was the last one.
+    template <bool IJK>
+    __device__ __forceinline__ bool step(int n_vox, double& l) {
         const double tn = fmin(tx, fmin(ty, tz));
-        const bool last = !(tn < t1);
-        if constexpr (IJK) f(k, ix, iy, iz, (last ? t1 : tn) - t);
-        else f(k, (last ? t1 : tn) - t);
+        const double end = t1;  // values: a select of fields would select addresses
+        const int dkx = kx, dky = ky, dkz = kz, sx = X.s, sy = Y.s, sz = Z.s;
+        const bool last = !(tn < end);
+        l = (last ? end : tn) - t;
         t = tn;
         const bool cx = tx == tn;
         const bool cy = !cx && ty == tn;
         const bool cz = !cx && !cy;
-        k += cx ? kx : (cy ? ky : kz);
+        k += cx ? dkx : (cy ? dky : dkz);
         if constexpr (IJK) {
-            ix += cx ? X.s : 0;
-            iy += cy ? Y.s : 0;
-            iz += cz ? Z.s : 0;
+            X.i += cx ? sx : 0;
+            Y.i += cy ? sy : 0;
+            Z.i += cz ? sz : 0;
         }
         X.n += cx ? 1.0 : 0.0;
         Y.n += cy ? 1.0 : 0.0;
@@ -123,7 +136,69 @@ __device__ __forceinline__ void seg_walk(const VoxArgs& A, const Box& b, double 
         tz = __fma_rn(Z.n, Z.dt, Z.t0);
         // (no crossing of the box's end comes before t1: the index test only
         // ends segments of non-finite numbers)
-        if (last || (unsigned)k >= (unsigned)A.n_vox) return;
+        return !last && (unsigned)k < (unsigned)n_vox;
+    }
+};
+
+// f(linear index, ix, iy, iz, length inside) of the segment's voxels.
+template <typename F>
+__device__ __forceinline__ void seg_walk(const VoxArgs& A, const Box& b, double px, double py, double pz, double vx,
+                                         double vy, double vz, double tmax, F&& f) {
+    SegWalk W;
+    if (!W.begin(A, b, px, py, pz, vx, vy, vz, tmax)) return;
+    for (bool on = true; on;) {
+        const int k = W.k, ix = W.X.i, iy = W.Y.i, iz = W.Z.i;
+        double l;
+        on = W.step<true>((int)A.n_vox, l);
+        f(k, ix, iy, iz, l);
+    }
+}
+
+// sum + the lengths of the segment's voxels times x[voxel], added in order.
+// The fetches bound it, so the walk runs SEG_AHEAD voxels at a time: while
+// the next ones are found, those of the last batch arrive (a batch's terms are
+// added one batch later; the lanes whose segment has ended step on, reading
+// voxel 0 and adding nothing).  Against one voxel ahead, with registers for
+// six wavefronts a SIMD instead of four: images of 64^3, 9 cameras 70 us (91),
+// of 127 x 90 x 77, 16 cameras 165 (188), transmittances 113 (114) and 335
+// (354).  Two and four voxels ahead are within 3%.
+constexpr int SEG_AHEAD = 3;
+
+__device__ __forceinline__ double seg_sum(const VoxArgs& A, const Box& b, double px, double py, double pz, double vx,
+                                          double vy, double vz, double tmax, const double* x, double sum) {
+    SegWalk W;
+    if (!W.begin(A, b, px, py, pz, vx, vy, vz, tmax)) return sum;
+    double xa[SEG_AHEAD], la[SEG_AHEAD], xb[SEG_AHEAD], lb[SEG_AHEAD];
+    bool on = true;
+    auto fetch = [&](double (&xs)[SEG_AHEAD], double (&ls)[SEG_AHEAD]) {
+        for (int i = 0; i < SEG_AHEAD; ++i) {
+            const int k = W.k;
+            xs[i] = x[on ? k : 0];
+            const bool more = W.step<false>((int)A.n_vox, ls[i]);
+            ls[i] = on ? ls[i] : -INFINITY;  // (no length of a voxel)
+            on = on && more;
+        }
+    };
+    auto add = [&](const double (&xs)[SEG_AHEAD], const double (&ls)[SEG_AHEAD]) {
+        for (int i = 0; i < SEG_AHEAD; ++i) {
+            const double s = sum + xs[i] * ls[i];
+            sum = ls[i] == -INFINITY ? sum : s;
+        }
+    };
+    fetch(xa, la);
+    for (;;) {
+        if (!on) {
+            add(xa, la);
+            return sum;
+        }
+        fetch(xb, lb);
+        add(xa, la);
+        if (!on) {
+            add(xb, lb);
+            return sum;
+        }
+        fetch(xa, la);
+        add(xb, lb);
     }
 }
 
@@ -134,13 +209,28 @@ __device__ __forceinline__ int64_t voxel_index(const VoxArgs& A, int ix, int iy,
 }
 
 // Line of sight from the centre of voxel (ix, iy, iz) to the camera: its
-// voxels in the domain.
-template <bool IJK, typename F>
-__device__ __forceinline__ void sight_walk(const VoxArgs& A, const HostCam& cam, int ix, int iy, int iz, F&& f) {
+// voxels in the domain (seg_walk), or their sum of beta times length.
+template <typename F>
+__device__ __forceinline__ void sight(const VoxArgs& A, const HostCam& cam, int ix, int iy, int iz, F&& f) {
     const double x = (ix + 0.5) * A.dx, y = (iy + 0.5) * A.dy, z = (iz + 0.5) * A.dz;
     const double Dx = cam.pos[0] - x, Dy = cam.pos[1] - y, Dz = cam.pos[2] - z;
     const double len = sqrt(Dx * Dx + Dy * Dy + Dz * Dz);
-    if (len > 0.0) seg_walk<IJK>(A, domain(A), x, y, z, Dx / len, Dy / len, Dz / len, len, f);
+    if (len > 0.0) f(x, y, z, Dx / len, Dy / len, Dz / len, len);
+}
+
+template <typename F>
+__device__ __forceinline__ void sight_walk(const VoxArgs& A, const HostCam& cam, int ix, int iy, int iz, F&& f) {
+    sight(A, cam, ix, iy, iz, [&](double x, double y, double z, double vx, double vy, double vz, double len) {
+        seg_walk(A, domain(A), x, y, z, vx, vy, vz, len, f);
+    });
+}
+
+__device__ __forceinline__ double sight_depth(const VoxArgs& A, const HostCam& cam, int ix, int iy, int iz) {
+    double tau = 0.0;
+    sight(A, cam, ix, iy, iz, [&](double x, double y, double z, double vx, double vy, double vz, double len) {
+        tau = seg_sum(A, domain(A), x, y, z, vx, vy, vz, len, A.beta, 0.0);
+    });
+    return tau;
 }
 
 // Camera of global pixel p (the last camera whose first pixel is <= p).
@@ -333,9 +423,9 @@ __device__ __forceinline__ bool visible(const VoxArgs& A, const HostCam& cam, co
 // is what they contribute.  Bound by the gathers of beta: the block's voxels
 // are spread over the grid (shorter last lines) while beta fits an XCD's 4 MB
 // of L2, and consecutive past it (64^3, 9 cameras: 113 us spread, 143
-// consecutive; 127 x 90 x 77, 16 cameras: 480 and 350).
+// consecutive; 127 x 90 x 77, 16 cameras: 480 and 335).
 template <bool SPREAD>
-__global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_transmittance(VoxArgs A) {
+__global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_transmittance(VoxArgs A) {
     __shared__ uint16_t s_list[VOX_CHUNK];
     __shared__ int s_n;
     for (int c = blockIdx.y; c < A.n_cams; c += gridDim.y) {
@@ -352,14 +442,7 @@ __global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_transmittance(VoxArgs A) {
             const int k = (int)chunk_voxel<SPREAD>(s_list[e]);
             int ix, iy, iz;
             voxel_of(A, k, ix, iy, iz);
-            // (a voxel's term is added a step after its fetch is issued)
-            double tau = 0.0, bp = 0.0, lp = 0.0;
-            sight_walk<false>(A, cam, ix, iy, iz, [&](int m, double l) {
-                tau += bp * lp;
-                bp = A.beta[m];
-                lp = l;
-            });
-            const double T = exp(-(tau + bp * lp));
+            const double T = exp(-sight_depth(A, cam, ix, iy, iz));
             if (A.T) A.T[off + k] = T;
             if (A.src) A.src[off + k] = A.j[off + k] * A.beta[k] * T;
         }
@@ -370,8 +453,8 @@ __global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_transmittance(VoxArgs A) {
 // i_c(p) = 1/(n^2 V) sum_rho sum_k l_rho(k) src_c(k), src = j beta T.  One
 // lane per sub-pixel ray (tpp lanes a pixel, at most a block's), summed in LDS:
 // with one lane per pixel the images of 9 cameras of 128^2 pixels were two
-// wavefronts a SIMD (64^3, 2 x 2 rays: 92 us, 270 before).
-__global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_project(VoxArgs A) {
+// wavefronts a SIMD (64^3, 2 x 2 rays: 92 us, 270 before; 70 with seg_sum).
+__global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_project(VoxArgs A) {
     __shared__ double s_acc[VOX_BLOCK];
     const double scale = 1.0 / ((double)A.n_side * A.n_side * A.dx * A.dy * A.dz);
     const int n2 = A.n_side * A.n_side;
@@ -391,14 +474,7 @@ __global__ void __launch_bounds__(VOX_BLOCK, 6) k_vox_project(VoxArgs A) {
             for (int r = sub; r < n2; r += tpp) {
                 double vx, vy, vz;
                 subpixel_dir(cam, row, col, r % A.n_side, r / A.n_side, A.n_side, vx, vy, vz);
-                double sp = 0.0, lp = 0.0;
-                seg_walk<false>(A, domain(A), cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
-                                [&](int k, double l) {
-                                    acc += lp * sp;
-                                    sp = src[k];
-                                    lp = l;
-                                });
-                acc += lp * sp;
+                acc = seg_sum(A, domain(A), cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY, src, acc);
             }
         }
         s_acc[threadIdx.x] = acc;
@@ -442,7 +518,7 @@ __global__ void __launch_bounds__(VOX_BLOCK) k_vox_near(VoxArgs A, double* out) 
             if (g == 0.0) continue;
             double vx, vy, vz;
             subpixel_dir(cam, (int)(lp / cam.width), (int)(lp % cam.width), r % n, r / n, n, vx, vy, vz);
-            seg_walk<true>(A, box, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
+            seg_walk(A, box, cam.pos[0], cam.pos[1], cam.pos[2], vx, vy, vz, INFINITY,
                            [&](int k, int ix, int iy, int iz, double l) {
                                if (COUNT && !(l > eps)) return;
                                const double x = COUNT ? 1.0 : g * l;
@@ -505,10 +581,12 @@ __device__ __forceinline__ double slab_length(const Slab& B, double vx, double v
 // B_c of the voxels outside the near box, gathered over the footprint of each
 // on the image: a few rays a voxel far from the camera (one lane), hundreds
 // next to the near box (a wavefront, 8 x 8 rays at a time).  No atomics, and
-// the sum of a voxel does not depend on the launch.  Bound by instructions
-// (VALU 33% of the slots: the lanes' footprints differ): 64^3, 9 cameras of
-// 128^2, 2 x 2 rays 302 us with the near pass's 58, against 3.86 ms of device
-// atomics; 127 x 90 x 77, 16 cameras of 160 x 120 741 + 84 us against 7.6 ms.
+// the sum of a voxel does not depend on the launch.  Bound by instructions (the
+// lanes' footprints differ) and the fetches of dl, each in flight while the
+// next ray's length is found: 64^3, 9 cameras of 128^2, 2 x 2 rays 292 us (315
+// with a wait for each) and the near pass's 58, against 3.86 ms of device
+// atomics; 127 x 90 x 77, 16 cameras of 160 x 120 669 (757) + 84 us against
+// 7.6 ms.
 // COUNT: the number of rays longer than eps.  Otherwise B is used at once: grad(k) += q T j B, and B
 // (scratch) becomes the weight w = T beta j B of the voxel's line of sight.
 constexpr double VOX_LIGHT = 64.0;
@@ -565,7 +643,7 @@ __global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_gather(VoxArgs A, double* 
         };
         // sum over the rays (s, r) of the range, strided
         auto gather = [&](const Slab& B, double s0, double s1, double r0, double r1, double step) {
-            double acc = 0.0;
+            double acc = 0.0, dp = 0.0, lp = 0.0;
             for (double r = r0; r <= r1; r += step) {
                 const double row = floor((r + 0.5) * in);
                 const double qy = (row + s_frac[(int)(r - row * n)] - cam.cy) * ify;
@@ -578,11 +656,16 @@ __global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_gather(VoxArgs A, double* 
                                                  __fma_rn(cam.R[2], qx, oz));
                     if (COUNT) {
                         if (l > eps) acc += 1.0;
-                    } else if (l > 0.0) {
-                        acc += dl[(int)row * cam.width + (int)col] * scale * l;
+                    } else {
+                        // (a ray's term is added when the next one's fetch is out)
+                        const double x = acc + dp * scale * lp;
+                        acc = lp > 0.0 ? x : acc;
+                        dp = dl[(int)row * cam.width + (int)col];
+                        lp = l;
                     }
                 }
             }
+            if (!COUNT && lp > 0.0) acc += dp * scale * lp;
             return acc;
         };
         for (int e = threadIdx.x; e < n_list; e += VOX_BLOCK) {
@@ -738,7 +821,7 @@ __global__ void __launch_bounds__(LOS_BLOCK, 6) k_vox_los_adjoint(VoxArgs A, int
         __syncthreads();
         const double* qc = A.q ? A.q + (int64_t)c * A.n_vox : nullptr;
         if (w != 0.0)
-            sight_walk<true>(A, cam, ix, iy, iz, [&](int m, int jx, int jy, int jz, double l) {
+            sight_walk(A, cam, ix, iy, iz, [&](int m, int jx, int jy, int jz, double l) {
                 const int s = (a == 0 ? jx : (a == 1 ? jy : jz)) - a0;
                 const int u = a == 0 ? jy : jx, v = a == 2 ? jy : jz;
                 if ((unsigned)s < (unsigned)n_s) {
