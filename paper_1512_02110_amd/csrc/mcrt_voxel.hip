@@ -703,13 +703,16 @@ __global__ void __launch_bounds__(VOX_BLOCK, 4) k_vox_gather(VoxArgs A, double* 
 // that the lines cross, which narrows from the tile to one voxel.  The beam
 // is added to the gradient at the end, so that a device atomic stands for
 // every voxel of the beam instead of every crossing of every line.  Bound by
-// instructions (VALU 50%): 64^3, 9 cameras 268 us against 2.64 ms with an
-// atomic per crossing, 127 x 90 x 77, 16 cameras 0.89 against 4.1 ms.  Slices
+// instructions and the blocks' barriers: 64^3, 9 cameras 240 us against 2.64 ms
+// with an atomic per crossing, 127 x 90 x 77, 16 cameras 0.75 against 4.1 ms
+// (275 us and 0.90 ms with a lane per rectangle and a division for each of its
+// 16 ends, which all wavefronts of the block wait for).  Slices
 // past the LDS copy's room, and a crossing that rounding puts outside its
 // rectangle, go to the gradient directly.
 constexpr int LOS_TILE = 8;
 constexpr int LOS_BLOCK = LOS_TILE * LOS_TILE * LOS_TILE;
 constexpr int LOS_SLICES = 256;
+static_assert(2 * LOS_SLICES <= LOS_BLOCK, "two lanes a slice");
 constexpr int LOS_CELLS = 4608;  // 36 KB: with the tables four blocks a CU
 
 __global__ void __launch_bounds__(LOS_BLOCK, 6) k_vox_los_adjoint(VoxArgs A, int tx, int ty) {
@@ -756,36 +759,45 @@ __global__ void __launch_bounds__(LOS_BLOCK, 6) k_vox_los_adjoint(VoxArgs A, int
             else a1 = a0 + LOS_SLICES;
         }
         const int n_s = a1 - a0;
-        for (int s = t; s < n_s; s += LOS_BLOCK) {
-            int r0[2], r1[2];
-            for (int d = 0; d < 2; ++d) {
-                const int ax = d == 0 ? (a == 0 ? 1 : 0) : (a == 2 ? 1 : 2);
-                const double Pd = ax == 0 ? P[0] : (ax == 1 ? P[1] : P[2]);
-                const int ld = ax == 0 ? lo[0] : (ax == 1 ? lo[1] : lo[2]);
-                const int hd = ax == 0 ? hi[0] : (ax == 1 ? hi[1] : hi[2]);
-                const int nd = ax == 0 ? n[0] : (ax == 1 ? n[1] : n[2]);
-                double m0 = INFINITY, m1 = -INFINITY;
-                if (Pa > la - 1.0 && Pa < ha + 1.0) {
-                    // the camera is level with the tile: the hull of both
-                    m0 = fmin(ld + 0.5, Pd);
-                    m1 = fmax(hd - 0.5, Pd);
-                } else {
-                    // the position X + (P - X)(z - Xa)/(Pa - Xa) is monotone
-                    // in X, Xa and z each: its extremes are at their ends
-                    for (int e = 0; e < 8; ++e) {
-                        const double X = e & 1 ? hd - 0.5 : ld + 0.5, Xa = e & 2 ? ha - 0.5 : la + 0.5;
-                        const double z = a0 + s + (e & 4 ? 1 : 0);
-                        const double f = fmin(fmax((z - Xa) / (Pa - Xa), 0.0), 1.0);
-                        const double x = X + (Pd - X) * f;
-                        m0 = fmin(m0, x);
-                        m1 = fmax(m1, x);
-                    }
+        // two lanes a slice, one for each of the rectangle's sides (LOS_BLOCK
+        // lanes for LOS_SLICES slices); the divisions by Pa - Xa once
+        const bool level = Pa > la - 1.0 && Pa < ha + 1.0;
+        const double X0 = la + 0.5, X1 = ha - 0.5;
+        const double iv0 = level ? 0.0 : 1.0 / (Pa - X0), iv1 = level ? 0.0 : 1.0 / (Pa - X1);
+        if (t < 2 * n_s) {
+            const int s = t >> 1, d = t & 1;
+            const int ax = d == 0 ? (a == 0 ? 1 : 0) : (a == 2 ? 1 : 2);
+            const double Pd = ax == 0 ? P[0] : (ax == 1 ? P[1] : P[2]);
+            const int ld = ax == 0 ? lo[0] : (ax == 1 ? lo[1] : lo[2]);
+            const int hd = ax == 0 ? hi[0] : (ax == 1 ? hi[1] : hi[2]);
+            const int nd = ax == 0 ? n[0] : (ax == 1 ? n[1] : n[2]);
+            double m0 = INFINITY, m1 = -INFINITY;
+            if (level) {
+                // the camera is level with the tile: the hull of both
+                m0 = fmin(ld + 0.5, Pd);
+                m1 = fmax(hd - 0.5, Pd);
+            } else {
+                // the position X + (P - X)(z - Xa)/(Pa - Xa) is monotone
+                // in X, Xa and z each: its extremes are at their ends
+                for (int e = 0; e < 8; ++e) {
+                    const double X = e & 1 ? hd - 0.5 : ld + 0.5;
+                    const double z = a0 + s + (e & 4 ? 1 : 0);
+                    const double f = fmin(fmax((z - (e & 2 ? X1 : X0)) * (e & 2 ? iv1 : iv0), 0.0), 1.0);
+                    const double x = X + (Pd - X) * f;
+                    m0 = fmin(m0, x);
+                    m1 = fmax(m1, x);
                 }
-                r0[d] = (int)fmin(fmax(floor(m0 - 1e-6), 0.0), (double)nd);
-                r1[d] = (int)fmin(fmax(floor(m1 + 1e-6) + 1.0, 0.0), (double)nd);
             }
-            s_sl[s] = make_int4(r0[0], r0[1], max(r1[0] - r0[0], 0), 0);
-            s_h[s] = max(r1[1] - r0[1], 0);
+            const int r0 = (int)fmin(fmax(floor(m0 - 1e-6), 0.0), (double)nd);
+            const int r1 = (int)fmin(fmax(floor(m1 + 1e-6) + 1.0, 0.0), (double)nd);
+            if (d == 0) {
+                s_sl[s].x = r0;
+                s_sl[s].z = max(r1 - r0, 0);
+                s_sl[s].w = 0;
+            } else {
+                s_sl[s].y = r0;
+                s_h[s] = max(r1 - r0, 0);
+            }
         }
         __syncthreads();
         if (t < 64) {
