@@ -279,6 +279,54 @@ __device__ __forceinline__ void dep_cross(Real tn, int& k, Real& tx, Real& ty, R
             : [tn] "v"(tn), [kx] "v"(kx), [ky] "v"(ky), [kz] "v"(kz), [dx] "v"(dtx), [dy] "v"(dty), [dz] "v"(dtz)
             : "vcc", "scc");
 }
+// The crossings of a flight's step in two parts: first the index k and the
+// crossings left c on each axis (what the next voxel's fetch needs), with the
+// lanes of each axis in mx, my and mz; then, on the lanes go (of these), r and
+// t of the crossed axis, the optical depth and the parameter.  Only lanes in
+// on, and of them the active ones, take part.
+#define MCRT_LEAVE(A) "v_add_u32 %[k], %[k" A "], %[k]\n\tv_add_u32 %[c" A "], -1, %[c" A "]\n\t"
+#define MCRT_FLIGHT_LEAVE(EQ)                                                                                      \
+    asm("s_mov_b64 %[ex], exec\n\ts_and_b64 exec, exec, %[on]\n\ts_mov_b64 %[mz], exec\n\t" EQ                       \
+        " vcc, %[tn], %[tx]\n\ts_mov_b64 %[mx], exec\n\t" MCRT_LEAVE("x")                                           \
+        "s_andn2_wrexec_b64 %[mz], %[mz]\n\t" EQ " vcc, %[tn], %[ty]\n\ts_mov_b64 %[my], exec\n\t" MCRT_LEAVE("y")  \
+        "s_andn2_wrexec_b64 %[mz], %[mz]\n\t" MCRT_LEAVE("z") "s_mov_b64 exec, %[ex]"                               \
+        : [ex] "=&s"(ex), [mx] "=&s"(mx), [my] "=&s"(my), [mz] "=&s"(mz), [k] "+v"(k), [cx] "+v"(cx), [cy] "+v"(cy), \
+          [cz] "+v"(cz)                                                                                            \
+        : [on] "s"(on), [tn] "v"(tn), [tx] "v"(tx), [ty] "v"(ty), [kx] "v"(kx), [ky] "v"(ky), [kz] "v"(kz)          \
+        : "vcc", "scc")
+template <typename Real>
+__device__ __forceinline__ void flight_leave(unsigned long long on, Real tn, Real tx, Real ty, uint32_t& k, int& cx,
+                                             int& cy, int& cz, int kx, int ky, int kz, unsigned long long& mx,
+                                             unsigned long long& my, unsigned long long& mz) {
+    unsigned long long ex;
+    if constexpr (sizeof(Real) == 4) MCRT_FLIGHT_LEAVE("v_cmpx_eq_f32");
+    else MCRT_FLIGHT_LEAVE("v_cmpx_eq_f64");
+}
+#undef MCRT_FLIGHT_LEAVE
+#undef MCRT_LEAVE
+
+#define MCRT_ENTER(ADD, MUL, A) \
+    "s_and_b64 exec, %[m" A "], %[go]\n\t" ADD " %[r" A "], %[s" A "], %[r" A "]\n\t" MUL " %[t" A "], %[r" A "], %[g" A "]\n\t"
+#define MCRT_FLIGHT_ENTER(ADD, MUL, MOV)                                                                           \
+    asm("s_mov_b64 %[ex], exec\n\t" MCRT_ENTER(ADD, MUL, "x") MCRT_ENTER(ADD, MUL, "y") MCRT_ENTER(ADD, MUL, "z")  \
+        "s_mov_b64 exec, %[go]\n\t" MOV " %[tau], %[taun]\n\t" MOV " %[t], %[tn]\n\ts_mov_b64 exec, %[ex]"          \
+        : [ex] "=&s"(ex), [rx] "+v"(rx), [ry] "+v"(ry), [rz] "+v"(rz), [tx] "+v"(tx), [ty] "+v"(ty), [tz] "+v"(tz), \
+          [tau] "+v"(tau), [t] "+v"(t)                                                                             \
+        : [mx] "s"(mx), [my] "s"(my), [mz] "s"(mz), [go] "s"(go), [sx] "v"(sx), [sy] "v"(sy), [sz] "v"(sz),        \
+          [gx] "v"(gx), [gy] "v"(gy), [gz] "v"(gz), [taun] "v"(taun), [tn] "v"(tn)                                 \
+        : "scc")
+template <typename Real>
+__device__ __forceinline__ void flight_enter(unsigned long long mx, unsigned long long my, unsigned long long mz,
+                                             unsigned long long go, Real& rx, Real& ry, Real& rz, Real& tx, Real& ty,
+                                             Real& tz, Real sx, Real sy, Real sz, Real gx, Real gy, Real gz, Real& tau,
+                                             Real taun, Real& t, Real tn) {
+    unsigned long long ex;
+    if constexpr (sizeof(Real) == 4) MCRT_FLIGHT_ENTER("v_add_f32", "v_mul_f32", "v_mov_b32");
+    else MCRT_FLIGHT_ENTER("v_add_f64", "v_mul_f64", "v_mov_b64");
+}
+#undef MCRT_FLIGHT_ENTER
+#undef MCRT_ENTER
+
 #undef MCRT_DEP
 #undef MCRT_CROSS_IN
 #undef MCRT_CROSS_OUT
@@ -476,13 +524,19 @@ constexpr int FLIGHT_GOES_ON = 4;
 constexpr uint32_t FLIGHT_BUDGET = 32;
 
 //
-// A step is branch free up to its end: the crossing out of the voxel is found
-// first and the fetch of the next voxel's extinction goes out (the zero after
-// the voxels when the photon leaves or enters an empty run), then this
-// voxel's extinction, fetched a step ago, decides whether the photon collides
-// here, and only then is the crossing committed.  The walk counts the
-// crossings left to the domain's face on each axis (c) instead of keeping the
-// voxel indices.
+// A step is branch free: the crossing out of the voxel is found first and the
+// fetch of the next voxel's extinction goes out (the zero after the voxels when
+// the photon leaves or enters an empty run), then this voxel's extinction,
+// fetched a step ago, decides whether the photon collides here, and only then
+// are r, t and the optical depth moved on (the index and the counts, which the
+// fetch needed, are taken back after the loop).  The walk counts the crossings
+// left to the domain's face on each axis (c) instead of keeping the voxel
+// indices.  Two steps per pass of the loop, the second on the lanes that still
+// fly: with a branch between them, or selects for every lane that has
+// collided, the compiler moved the fetch behind the decision (a wait for
+// memory every step).  With the crossings under lane masks the collision pass
+// of 1e6 photons on 64^3 takes 2.67 ms (2.96 before), mixed renders 6% less
+// and FP32 renders of 64^3 3% less.
 //
 // DEP: also subtract dep times the length flown in every voxel from grad
 // (the free-flight score of the full mixture gradient).
@@ -508,56 +562,73 @@ __device__ __forceinline__ int free_flight(const KArgs<Real>& A, const uint32_t*
     const int kx = W.kx, ky = W.ky, kz = W.kz;
     uint32_t k = (uint32_t)W.k;
     Real rx = W.rx, ry = W.ry, rz = W.rz, tx = W.tx, ty = W.ty, tz = W.tz, t = (Real)0;
-    Real tau = (Real)0, b_hit = (Real)0;
-    Real b = beta_at(A, MASK ? mask : nullptr, W.k, W.iz);
+    Real tau = (Real)0;
+    Real b0 = beta_at(A, MASK ? mask : nullptr, W.k, W.iz), b1 = (Real)0;
     uint32_t n = 0;
-    bool hit, away, cz_last;
-    do {
+    bool hit, away, flies;
+    using u64 = unsigned long long;
+    // One voxel, on the lanes in on: b its extinction, fetched a step ago, bn
+    // the next one's; takes the lanes that collide or leave out of on.
+    auto step = [&](u64& on, u64& hits, const Real& b, Real& bn) {
         const Real tn = fmin(tx, fmin(ty, tz));
-        const bool cx = tx == tn;
-        const bool cy = !cx && ty == tn;
-        const bool cz = !cx && !cy;
-        const int mx = cnx - (cx ? 1 : 0), my = cny - (cy ? 1 : 0), mz = cnz - (cz ? 1 : 0);
-        away = (mx | my | mz) < 0;
-        const uint32_t kn = k + (uint32_t)(cx ? kx : (cy ? ky : kz));
+        const uint32_t k_here = k;
+        u64 mx, my, mz;
+        flight_leave(on, tn, tx, ty, k, cnx, cny, cnz, kx, ky, kz, mx, my, mz);
+        away = (cnx | cny | cnz) < 0;
+        const uint32_t kn = k;
         uint32_t ld = away ? n_vox : kn;
         if constexpr (MASK) {
             const uint32_t kk = away ? 0u : kn;  // (voxel 0 is a valid index to test)
             const bool occ = __builtin_amdgcn_ubfe(mask[kk >> msh5], kk >> A.msh, 1u) != 0u;
-            const int iz = W.sz > 0 ? A.G.nz - 1 - mz : mz;
+            const int iz = W.sz > 0 ? A.G.nz - 1 - cnz : cnz;
             ld = occ ? ld : (AIR && !away ? empty_index(A, iz) : n_vox);
         }
-        const Real bn = A.beta[ld];
+        bn = A.beta[ld];
+        __builtin_amdgcn_sched_barrier(0);  // the fetch goes out here, before the wait for b
         const Real seg = tn - t;
         const Real tau_n = tau + b * seg;
-        hit = b > (Real)0 && tau_n >= taustar;
-        if (DEP && dep != 0.0 && !hit) unsafeAtomicAdd(grad + k, -dep * (double)seg);
-        b_hit = b;
-        b = bn;
-        tau = hit ? tau : tau_n;
-        t = hit ? t : tn;
-        k = hit ? k : kn;
-        cnx = hit ? cnx : mx;
-        cny = hit ? cny : my;
-        cnz = hit ? cnz : mz;
-        rx += cx && !hit ? W.sfx : (Real)0;
-        ry += cy && !hit ? W.sfy : (Real)0;
-        rz += cz && !hit ? W.sfz : (Real)0;
-        tx = rx * W.gx;
-        ty = ry * W.gy;
-        tz = rz * W.gz;
-        cz_last = cz;
-        ++n;
-    } while (!(hit || away) && n < budget);
+        const u64 h = on & __builtin_amdgcn_ballot_w64(b > (Real)0) & __builtin_amdgcn_ballot_w64(tau_n >= taustar);
+        const u64 go = on & ~h;
+        if (DEP && dep != 0.0 && __builtin_amdgcn_inverse_ballot_w64(go))
+            unsafeAtomicAdd(grad + k_here, -dep * (double)seg);
+        flight_enter(mx, my, mz, go, rx, ry, rz, tx, ty, tz, W.sfx, W.sfy, W.sfz, W.gx, W.gy, W.gz, tau, tau_n, t, tn);
+        hits |= h;
+        on = go & ~__builtin_amdgcn_ballot_w64(away);
+    };
+    // (in pairs, so that the two extinctions need not change registers, which
+    // would wait for the fetch; the budget is even, or no budget)
+    do {
+        u64 on = __builtin_amdgcn_ballot_w64(true), hits = 0ull;
+        step(on, hits, b0, b1);
+        step(on, hits, b1, b0);
+        hit = __builtin_amdgcn_inverse_ballot_w64(hits);
+        flies = __builtin_amdgcn_inverse_ballot_w64(on);
+        n += 2;
+    } while (flies && n < budget);
+    // (the fetch counts as used by every lane: used only by the lanes that fly
+    // on, it is moved to where the others have left, i.e. behind the wait for
+    // the fetch before it, and no two are in flight)
+    asm volatile("" ::"v"(b0));
+    if (hit) {  // the crossing was not made
+        const Real tn = fmin(tx, fmin(ty, tz));
+        const bool cx = tx == tn, cy = !cx && ty == tn, cz = !cx && !cy;
+        k -= (uint32_t)(cx ? kx : (cy ? ky : kz));
+        cnx += cx ? 1 : 0;
+        cny += cy ? 1 : 0;
+        cnz += cz ? 1 : 0;
+    }
     // a voxel per crossing, and the one of the collision
     vfree += (uint32_t)((c0x - cnx) + (c0y - cny) + (c0z - cnz)) + (hit ? 1u : 0u);
     if (!hit && away) {
         ph.t_exit = t;
-        return cz_last ? (W.sz > 0 ? 1 : 2) : 3;
+        return cnz < 0 ? (W.sz > 0 ? 1 : 2) : 3;
     }
     Real tc = t;
     if (hit) {
-        tc = t + (taustar - tau) / b_hit;
+        // (read again: kept, the extinctions of both steps would need registers
+        // of their own)
+        const Real b = beta_at(A, MASK ? mask : nullptr, (int)k, W.sz > 0 ? A.G.nz - 1 - cnz : cnz);
+        tc = t + (taustar - tau) / b;
         if (DEP && dep != 0.0) unsafeAtomicAdd(grad + k, -dep * (double)(tc - t));
     }
     ph.fx = walk_frac(f0x, W.sfx, rx, wx, A.G.idx, tc);
