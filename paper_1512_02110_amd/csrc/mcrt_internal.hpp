@@ -114,7 +114,8 @@ struct KArgs {
     uint32_t max_events;
     uint64_t seed, pid0, n_photons;
     unsigned long long* work;   // photon counter (zeroed before launch)
-    uint32_t fetch_block;       // photon ids a wavefront takes per fetch (set at launch)
+    // photon ids a wavefront starts with and takes per fetch (set at launch)
+    uint32_t fetch_first, fetch_block;
     unsigned long long* stats;  // ST_N counters (zeroed before launch)
     double* img;                // raw local-estimate sums (F64 tally)
     double* img_m2;             // optional: raw sums of squared local estimates

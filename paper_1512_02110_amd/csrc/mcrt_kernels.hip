@@ -73,35 +73,51 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long mask) {
     return (uint32_t)__popcll(mask & __lanemask_lt());
 }
 
-// Photon ids for the lanes in `need`, in order, from the wavefront's pool
-// [pool_next, pool_end), which is refilled `block` ids at a time with one
-// atomic on the global counter (a returning device atomic takes
-// microseconds; one per photon phase would stall every phase).  Called by
-// the whole wavefront, so that the pool stays uniform.  One refill must
-// cover every lane that still needs an id, so a block holds at least WAVE
-// ids; within that, the launch sets it so that every wavefront fetches about
-// 32 times (at most 256 ids): a launch ends with its slowest wavefront, and
-// a few large blocks per wavefront leave the others idle at the end.
+// Photon ids 0 .. n - 1 for the lanes in `need`, in order, from the
+// wavefront's pool [next, end): at first its own share `first` of the ids,
+// then blocks of `block` ids that one atomic on the global counter takes (ids
+// from n on: there are no more).  Called by the whole wavefront, so that the
+// pool stays uniform.  One refill must cover every lane that still needs an
+// id, so both hold at least WAVE ids.
+//
+// Returning atomics on one word are served one after the other, one in about
+// 38 ns: thousands of wavefronts that take their first ids so, and ask once
+// more at the end, wait for each other longer than a small launch works
+// (render of 16^3 194 us, with the first ids dealt out 171).  A look at the
+// counter before each atomic made it far worse (collision pass 9.4 ms, 2.6
+// without).  The blocks are 1/32 of a wavefront's share (at most 256 ids): a
+// launch ends with its slowest wavefront, and a few large blocks per wavefront
+// leave the others idle at the end.
 constexpr uint32_t FETCH_BLOCK_MAX = 256;
 
-__device__ __forceinline__ uint64_t wave_fetch(unsigned long long* work, uint32_t block, unsigned long long need,
-                                               uint64_t& pool_next, uint64_t& pool_end) {
+struct IdPool {
+    uint64_t next, end;
+};
+
+__device__ __forceinline__ IdPool id_pool(uint32_t first, uint32_t wave) {
+    const uint32_t wave_id = __builtin_amdgcn_readfirstlane(wave);  // (the pool stays in scalar registers)
+    return IdPool{(uint64_t)first * wave_id, (uint64_t)first * (wave_id + 1ull)};
+}
+
+__device__ __forceinline__ uint64_t wave_fetch(unsigned long long* work, uint32_t first, uint32_t block, uint32_t waves,
+                                               uint64_t n_ids, unsigned long long need, IdPool& pool) {
     const uint32_t n = (uint32_t)__popcll(need);
     const uint32_t rank = lanes_below(need);
-    const uint64_t left = pool_end - pool_next;
+    const uint64_t left = pool.end - pool.next;
     const uint32_t avail = left < n ? (uint32_t)left : n;
-    uint64_t id = pool_next + rank;
+    uint64_t id = pool.next + rank;
     if (avail < n) {
-        unsigned long long base = 0;
-        if (__lane_id() == 0) base = atomicAdd(work, (unsigned long long)block);
-        const unsigned lo = __shfl((unsigned)base, 0);
-        const unsigned hi = __shfl((unsigned)(base >> 32), 0);
-        pool_next = ((uint64_t)hi << 32) | lo;
-        pool_end = pool_next + block;
-        if (rank >= avail) id = pool_next + (rank - avail);
-        pool_next += n - avail;
+        const uint64_t shared = (uint64_t)first * waves;  // the ids from here on are shared out
+        unsigned long long base = n_ids;
+        if (shared < n_ids && __lane_id() == 0) base = shared + atomicAdd(work, (unsigned long long)block);
+        const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)base, 0);
+        const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(base >> 32), 0);
+        pool.next = ((uint64_t)hi << 32) | lo;
+        pool.end = pool.next + block;
+        if (rank >= avail) id = pool.next + (rank - avail);
+        pool.next += n - avail;
     } else {
-        pool_next += n;
+        pool.next += n;
     }
     return id;
 }
@@ -1221,13 +1237,13 @@ __global__ void __launch_bounds__((RenderThreads<MODE>::value), (RenderWaves<Rea
     Photon<Real> ph;
     Job<W> J{};
     bool alive = false, exhausted = false, busy = false, fin = false;
-    uint64_t pool_next = 0, pool_end = 0;
     uint32_t qhead = 0, qtail = 0;
     uint32_t n_ev = 0, n_le = 0;
     uint32_t kloc = 0;  // the lane's photon within the launch (tape replay)
     uint64_t vfree = 0, vconn = 0;
     uint64_t vconn_w = 0;  // counted per wavefront (the same in every lane)
     const uint32_t wave_id = blockIdx.x * NW + threadIdx.x / WAVE;
+    IdPool pool = id_pool(A.fetch_first, wave_id);
     const uint32_t w_first = MODE == MODE_TAPE || MODE == MODE_RTAPE ? wave_id * A.tp.rw : 0u;
     uint32_t w_used = 0;
     uint32_t wstep = 0;  // the wavefront's walk steps (gather capture)
@@ -1239,7 +1255,8 @@ __global__ void __launch_bounds__((RenderThreads<MODE>::value), (RenderWaves<Rea
     for (;;) {
         const unsigned long long need = __ballot(!alive && !exhausted);
         if (need) {
-            const uint64_t k = wave_fetch(A.work, A.fetch_block, need, pool_next, pool_end);
+            const uint64_t k =
+                wave_fetch(A.work, A.fetch_first, A.fetch_block, gridDim.x * NW, A.n_photons, need, pool);
             if (!alive && !exhausted) {
                 if (k < A.n_photons) {
                     launch_photon(A, A.pid0 + k, ph);
@@ -2031,7 +2048,7 @@ __global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
     const uint64_t total = (uint64_t)A.n_pix * A.n_pp;
     uint32_t n_ev = 0;
     uint64_t vfree_w = 0;  // counted per wavefront
-    uint64_t pool_next = 0, pool_end = 0;
+    IdPool pool = id_pool(A.fetch_first, (blockIdx.x * BLOCK + threadIdx.x) / WAVE);
     Photon<Real> ph;
     ph.ix = ph.iy = ph.iz = 0;
     ph.air = 0;
@@ -2163,7 +2180,8 @@ __global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
             if (need == 0ull) break;
             if (n_list == 0u) {
                 if (exhausted) break;
-                const uint64_t id = wave_fetch(A.work, A.fetch_block, ~0ull, pool_next, pool_end);
+                const uint64_t id = wave_fetch(A.work, A.fetch_first, A.fetch_block, gridDim.x * (BLOCK / WAVE), total,
+                                               ~0ull, pool);
                 Photon<Real> np;
                 int64_t p = 0;
                 const bool in = id < total && bmc_launch(A, id, p, np);
@@ -2532,7 +2550,7 @@ template <typename Real>
 __global__ void __launch_bounds__(BLOCK, sizeof(Real) == 4 ? 4 : 2) k_mix_path(KArgs<Real> A) {
     const uint32_t w = A.mix_evcap + 1u;
     const uint32_t n_vox = (uint32_t)A.n_vox;
-    uint64_t pool_next = 0, pool_end = 0;
+    IdPool pool = id_pool(A.fetch_first, (blockIdx.x * BLOCK + threadIdx.x) / WAVE);
     bool exhausted = false;
     Photon<Real> ph;
     double ffd = 0.0;
@@ -2570,7 +2588,8 @@ __global__ void __launch_bounds__(BLOCK, sizeof(Real) == 4 ? 4 : 2) k_mix_path(K
         for (;;) {
             const unsigned long long need = __ballot(state == MIX_NONE && !exhausted);
             if (need == 0ull) break;
-            const uint64_t k = wave_fetch(A.work, A.fetch_block, need, pool_next, pool_end);
+            const uint64_t k = wave_fetch(A.work, A.fetch_first, A.fetch_block, gridDim.x * (BLOCK / WAVE), A.n_photons,
+                                          need, pool);
             if (state == MIX_NONE && !exhausted) {
                 if (k >= A.n_photons) {
                     exhausted = true;
@@ -2856,17 +2875,30 @@ size_t render_dyn_lds(const KArgs<Real>& a, int mode) {
     return bytes;
 }
 
-// Ids a wavefront takes per fetch (see wave_fetch).
-static uint32_t fetch_block(int grid, int threads, uint64_t n) {
-    const uint64_t waves = (uint64_t)std::max(grid, 1) * (threads / WAVE);
-    return (uint32_t)std::min<uint64_t>(FETCH_BLOCK_MAX, std::max<uint64_t>(WAVE, n / (32 * waves)));
+// The ids a wavefront starts with and takes per fetch (see wave_fetch).
+// Photons start anywhere, so half of them are dealt out (three quarters: the
+// 1e7-photon render 5% slower, its wavefronts not equally fast).  Backward
+// packets of one pixel are alike and stay together, so they are dealt out by
+// the block only (half: 40-70% slower on 64^3), in larger blocks where a
+// wavefront fetches a few times only.  Where the first blocks leave less than a
+// quarter of a block per wavefront, all ids are dealt out evenly: every
+// wavefront would ask for the rest, and most in vain.
+template <typename Real>
+static void set_fetch(KArgs<Real>& a, int grid, int threads, uint64_t n, bool bmc = false) {
+    const uint64_t waves = (uint64_t)std::max(grid, 1) * (threads / WAVE), share = n / waves;
+    const uint64_t least = bmc && share >= 3 * WAVE && share < 8 * WAVE ? 2 * WAVE : WAVE;
+    const uint64_t block = std::min<uint64_t>(FETCH_BLOCK_MAX, std::max<uint64_t>(least, share / 32));
+    uint64_t first = bmc ? block : std::max<uint64_t>(block, share / 2);
+    if (4 * share < 5 * WAVE) first = std::max<uint64_t>(WAVE, share + 1);
+    a.fetch_block = (uint32_t)block;
+    a.fetch_first = (uint32_t)std::min<uint64_t>(0x7fffffffu, first);
 }
 
 template <typename Real, int MODE, int TALLY, bool AIRZ = false, bool W32 = false, bool CAP = false>
 static hipError_t launch_r(const KArgs<Real>& a, int grid, hipStream_t s) {
     const size_t dyn = render_dyn_lds(a, MODE);
     KArgs<Real> b = a;
-    b.fetch_block = fetch_block(grid, RenderThreads<MODE>::value, a.n_photons);
+    set_fetch(b, grid, RenderThreads<MODE>::value, a.n_photons);
     hipLaunchKernelGGL((k_render<Real, MODE, TALLY, AIRZ, W32, CAP>), dim3(grid), dim3(RenderThreads<MODE>::value),
                        dyn, s, b);
     return hipGetLastError();
@@ -2880,7 +2912,7 @@ template <typename Real>
 hipError_t launch_mix_path(const KArgs<Real>& a, int grid, hipStream_t s) {
     if (grid <= 0) return hipSuccess;
     KArgs<Real> b = a;
-    b.fetch_block = fetch_block(grid, BLOCK, a.n_photons);
+    set_fetch(b, grid, BLOCK, a.n_photons);
     hipError_t e = launch_fill_u64(a.work, 1, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_mix_path<Real>, dim3(grid), dim3(BLOCK), 0, s, b);
@@ -2932,7 +2964,7 @@ hipError_t launch_transport(const KArgs<Real>& a, int mode, int tally, int grid,
     if (mode == MODE_VOXEL) return launch_r<Real, MODE_VOXEL, TALLY_F64>(a, grid, s);
     if (mode == MODE_BMC) {
         KArgs<Real> b = a;
-        b.fetch_block = fetch_block(grid, BLOCK, (uint64_t)a.n_pix * a.n_pp);
+        set_fetch(b, grid, BLOCK, (uint64_t)a.n_pix * a.n_pp, true);
         hipLaunchKernelGGL(k_bmc<Real>, dim3(grid), dim3(BLOCK), 0, s, b);
         return hipGetLastError();
     }
