@@ -1114,17 +1114,28 @@ void tape_release(mc_tape* t, hipStream_t stream) {
 // upward cameras alone run 1.3-1.7 times as fast z fastest as x fastest
 // (replayed addresses: 640 -> 1068 G loads/s on a 64^3 cloud, 458 -> 736 on
 // 128^3, 356 -> 508 on 256 x 256 x 128).
+//
+// The bitmask's runs of 2^msh voxels lie along the same axis, and clouds are
+// flatter than wide: a run that is a large part of a column is empty far less
+// often than one along x, and every voxel of a run that is not empty is
+// fetched.  So the view's axis is taken only where a run is at most an eighth
+// of the grid along it: 128^3 (runs of 16) 169 -> 145 ms, but 256 x 256 x 128
+// (runs of 64, half a column) with scattered clouds and 36 cameras 275 -> 407
+// ms (with one cloud that fills the grid it gained 16%; not taken).
 template <typename Real>
-void view_layout(int n_cams, const mc_camera* cams, DevGrid<Real>& G) {
+void view_layout(int n_cams, const mc_camera* cams, int msh, DevGrid<Real>& G) {
     double along[3] = {0.0, 0.0, 0.0};
     for (int i = 0; i < n_cams; ++i)
         for (int a = 0; a < 3; ++a)
             along[a] += std::fabs(cams[i].R[6 + a]) * (double)cams[i].width * (double)cams[i].height;
+    const auto short_runs = [msh](int n) { return msh == 0 || ((int64_t)8 << msh) <= n; };
     if (along[2] >= along[1] && along[2] >= along[0]) {
+        if (!short_runs(G.nz)) return;
         G.lz = 1;
         G.lx = G.nz;
         G.ly = G.nz * G.nx;
     } else if (along[1] > along[0]) {
+        if (!short_runs(G.ny)) return;
         G.ly = 1;
         G.lx = G.ny;
         G.lz = G.nxy;
@@ -1484,7 +1495,7 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
     // walks and the bins read it (a mixture's fields, the LDS gradient's walk
     // and the capture keep x fastest)
     if (!mix && !cap && (mode == MODE_RENDER || mode == MODE_VOXEL || (mode == MODE_GRAD && A.tape)))
-        view_layout(n_cams, cams, A.G);
+        view_layout(n_cams, cams, msh, A.G);
     A.G32.lx = A.G.lx;
     A.G32.ly = A.G.ly;
     A.G32.lz = A.G.lz;

@@ -16,7 +16,7 @@
 //     direction and length to the camera, prefactor, pixel) into the
 //     wavefront's LDS queue, compacted with ballot/prefix counts.
 //   * Job phase: the 64 lanes walk connection rays taken from the queue.
-//     Lanes that finish are refilled together once 16 are idle, so the walk
+//     Lanes that finish are refilled together once 32 are idle, so the walk
 //     runs with nearly full wavefronts whatever the ray lengths and the
 //     number of cameras each collision is visible from.  A lane keeps an
 //     unfinished ray across photon phases.
@@ -2533,7 +2533,8 @@ __device__ __forceinline__ double mix_event_sums(const KArgs<Real>& A, const Pho
 // flights and new photons (those with a non-zero row, taken from the launch's
 // counter) are done together.
 //
-// For 1e6 photons on a 64^3 cloud with 9 cameras the scores take 3.0 ms; with
+// For 1e6 photons on a 64^3 cloud with 9 cameras the scores take 2.4 ms (3.0
+// with every photon from the common counter); with
 // a flight per pass of the loop, the photons dealt out beforehand and in two
 // launches, and one lane walking a later collision's cameras, they took 7.8
 // (one launch and this loop alone 5.75).  The atomics (2e7) would take 0.9 ms;
