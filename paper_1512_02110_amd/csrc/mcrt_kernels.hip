@@ -2134,7 +2134,6 @@ __global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
             W.ty = C.ty;
             W.tz = C.tz;
             W.t = C.t;
-            star = (Real)INFINITY;
             tau_s = 0.0;
             b = A.beta[W.k];
             // (a walk that cannot start adds nothing)
@@ -2251,9 +2250,11 @@ __global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
             if ((uint32_t)__popcll(m) <= keep) break;
             vfree_w += (uint32_t)__popcll(m & m_f);
             if (act) {
-                // branch free: a flight has no texit and a sun walk no star
-                // (both infinite).  The next voxel's fetch goes out before
-                // this one's extinction is needed, and the crossing is
+                // branch free: a flight has no texit (it is infinite), and only
+                // a flight collides: a sun walk's depth may be infinite (an
+                // infinite extinction, or a sum past the type's range) and its
+                // estimate is then zero.  The next voxel's fetch goes out
+                // before this one's extinction is needed, and the crossing is
                 // committed unless the photon collides first.
                 bool cx, cy, cz;
                 const Real tn = walk_next(W, cx, cy, cz);
@@ -2267,7 +2268,7 @@ __global__ void __launch_bounds__(BLOCK, 3) k_bmc(KArgs<Real> A) {
                                          : last || (uint32_t)k >= (uint32_t)A.n_vox;
                 const Real bn = A.beta[away ? (uint32_t)A.n_vox : (uint32_t)k];
                 const Real t2 = tau + b * l;
-                const bool hit = b > (Real)0 && t2 >= star;
+                const bool hit = flight && b > (Real)0 && t2 >= star;
                 tau_s += (double)b * (double)l;
                 tau = hit ? tau : t2;
                 b_hit = hit ? b : b_hit;
