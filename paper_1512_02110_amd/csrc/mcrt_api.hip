@@ -1548,7 +1548,7 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
                 h.pix_off = off;
                 off += (int64_t)c.width * c.height;
             }
-            CHECK_HIP(launch_vox_cams(ch, hc, stream));
+            CHECK_HIP(launch_vox_cams(ch, hc, nullptr, stream));
         }
         A.hcams = hc;
     } else if (mode == MODE_VOXEL) {
@@ -1848,13 +1848,18 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
     Scratch S;
     VoxArgs A;
     std::memset(&A, 0, sizeof(A));
-    int64_t max_rays = 0;  // of one camera
-    size_t bytes = round256(sizeof(HostCam) * n_cams) + round256(sizeof(VoxView) * n_cams) + 256;
+    int64_t max_pix = 0;  // of one camera
+    // (with the images and the gradient of a loop step asking for the same
+    // size, the pool hands one block back and forth: 0.1 ms a step of mc_recover)
+    size_t bytes = round256(sizeof(HostCam) * n_cams) + round256(sizeof(VoxView) * n_cams) +
+                   round256(sizeof(VoxRect) * n_cams) + 256;
     if (!counts && !(grad && keep_T)) bytes += round256(sizeof(double) * n_cv);
     if (grad) bytes += round256(sizeof(double) * n_cv);
     CHECK_HIP(lib_alloc((void**)&S.base, bytes, stream));
     {
         HostCam* dcams = S.take<HostCam>(n_cams);
+        VoxRect* dl_box = S.take<VoxRect>(n_cams);
+        A.dl_box = grad ? dl_box : nullptr;
         int64_t off = 0;
         for (int first = 0; first < n_cams; first += CAM_CHUNK) {
             CamChunk ch;
@@ -1875,12 +1880,12 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
                 h.pix_off = off;
                 off += (int64_t)c.width * c.height;
             }
-            CHECK_HIP(launch_vox_cams(ch, dcams, stream));
+            CHECK_HIP(launch_vox_cams(ch, dcams, A.dl_box, stream));
         }
         A.cams = dcams;
         A.n_pix = off;
         for (int i = 0; i < n_cams; ++i)
-            max_rays = std::max(max_rays, (int64_t)cams[i].width * cams[i].height * n_side * n_side);
+            max_pix = std::max(max_pix, (int64_t)cams[i].width * cams[i].height);
     }
     A.nx = grid->nx;
     A.ny = grid->ny;
@@ -1902,7 +1907,7 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
     if (counts) {
         // ray counts only (the conditioning)
         CHECK_HIP(launch_fill_f64(counts, n_cv, stream));
-        CHECK_HIP(launch_vox_backproject(A, counts, true, max_rays, stream));
+        CHECK_HIP(launch_vox_backproject(A, counts, true, max_pix, stream));
         goto done;
     }
     // the images take T with its source factors, the gradient T alone; a loop
@@ -1920,7 +1925,7 @@ int run_voxel(const mc_grid* grid, const double* beta, int n_cams, const mc_came
         A.grad = grad;
         CHECK_HIP(launch_fill_f64(A.B, n_cv, stream));
         CHECK_HIP(launch_fill_f64(grad, n_vox, stream));
-        CHECK_HIP(launch_vox_backproject(A, A.B, false, max_rays, stream));
+        CHECK_HIP(launch_vox_backproject(A, A.B, false, max_pix, stream));
         CHECK_HIP(launch_vox_los_adjoint(A, stream));
     }
 done:

@@ -263,6 +263,11 @@ struct VoxView {
     int pad_;
 };
 
+// Sub-pixel columns s0 .. s1 and rows r0 .. r1 of an image (s0 > s1: none).
+struct VoxRect {
+    double s0, r0, s1, r1;
+};
+
 struct VoxArgs {
     int nx, ny, nz;
     double dx, dy, dz;
@@ -270,6 +275,7 @@ struct VoxArgs {
     const double* beta;
     const HostCam* cams;
     const VoxView* views;
+    VoxRect* dl_box;            // per camera: the rays of the pixels with dl != 0 (gradient only)
     int n_cams;
     int n_side;                 // sub-pixel rays per side (n_side^2 per pixel)
     int64_t n_pix;
@@ -282,11 +288,11 @@ struct VoxArgs {
     const double* q;            // [camera][voxel] weights of the camera terms (nullable)
     double* grad;
 };
-hipError_t launch_vox_cams(const CamChunk& chunk, HostCam* dev, hipStream_t s);
+hipError_t launch_vox_cams(const CamChunk& chunk, HostCam* dev, VoxRect* dl_box, hipStream_t s);
 hipError_t launch_vox_views(const VoxArgs& a, VoxView* views, hipStream_t s);
 hipError_t launch_vox_transmittance(const VoxArgs& a, hipStream_t s);
 hipError_t launch_vox_project(const VoxArgs& a, hipStream_t s);
-hipError_t launch_vox_backproject(const VoxArgs& a, double* out, bool count, int64_t max_rays, hipStream_t s);
+hipError_t launch_vox_backproject(const VoxArgs& a, double* out, bool count, int64_t max_pix, hipStream_t s);
 hipError_t launch_vox_los_adjoint(const VoxArgs& a, hipStream_t s);
 hipError_t launch_vox_invert(double* x, int64_t n, hipStream_t s);
 hipError_t launch_reg(int nx, int ny, int nz, const double* beta, const double* w_layer, double eta, double* r,
