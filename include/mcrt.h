@@ -475,6 +475,14 @@ int mc_capture_gathers(const mc_grid* grid, const float* beta, int n_cams, const
                        uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves,
                        mc_stats* stats, void* hip_stream);
 
+/* The same on mc_render's own copy of beta and its runs: the indices that
+ * mc_render's walks ask for, voxel (x, y, z) at index strides[0] x +
+ * strides[1] y + strides[2] z (strides: host, 3 values, out). */
+int mc_capture_render_gathers(const mc_grid* grid, const float* beta, int n_cams, const mc_camera* cams,
+                              const mc_params* params, double* images, uint32_t first_step, uint32_t n_steps,
+                              uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves,
+                              int32_t* strides, mc_stats* stats, void* hip_stream);
+
 /* Static description of a status code. */
 const char* mc_error_string(int code);
 

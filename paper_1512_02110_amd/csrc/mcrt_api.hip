@@ -139,16 +139,18 @@ bool plain_walk_loads() {
     return v && v[0] == '1';
 }
 
-// An air + aerosol mixture: device fields of the reference channel and the
-// channel's aerosol cross-section ratio (Eq. channelBeta).
 // The gather capture (mc_capture_gathers): where the walks' loaded indices go.
 struct CaptureArgs {
     uint32_t* idx;
     uint32_t* steps;
     uint32_t first, n_steps, max_waves;
-    uint32_t n_waves;  // out: wavefronts of the launch
+    bool view;          // on the render's own copy of beta (else x fastest)
+    uint32_t n_waves;   // out: wavefronts of the launch
+    int32_t stride[3];  // out: index steps of the copy
 };
 
+// An air + aerosol mixture: device fields of the reference channel and the
+// channel's aerosol cross-section ratio (Eq. channelBeta).
 struct MixIn {
     const double* air;
     const double* aer;
@@ -1493,12 +1495,17 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
     mix_tape = mode == MODE_MIXGRAD && A.tape;
     // the copy of beta: laid out along the cameras' view where only the queued
     // walks and the bins read it (a mixture's fields, the LDS gradient's walk
-    // and the capture keep x fastest)
-    if (!mix && !cap && (mode == MODE_RENDER || mode == MODE_VOXEL || (mode == MODE_GRAD && A.tape)))
+    // and mc_capture_gathers keep x fastest)
+    if (!mix && (!cap || cap->view) && (mode == MODE_RENDER || mode == MODE_VOXEL || (mode == MODE_GRAD && A.tape)))
         view_layout(n_cams, cams, msh, A.G);
     A.G32.lx = A.G.lx;
     A.G32.ly = A.G.ly;
     A.G32.lz = A.G.lz;
+    if (cap) {
+        cap->stride[0] = A.G.lx;
+        cap->stride[1] = A.G.ly;
+        cap->stride[2] = A.G.lz;
+    }
     if (mode != MODE_TRACE && mode != MODE_BMC) mask = S.take<uint32_t>(mask_words);
     A.mask = mask;
     if (!mix) {
@@ -2009,10 +2016,10 @@ int mc_render_noalloc(const mc_grid* grid, const void* beta, int n_cams, const m
                       0, 0, nullptr, nullptr, nullptr, s, nullptr, nullptr, 0, nullptr, nullptr, fixed);
 }
 
-int mc_capture_gathers(const mc_grid* grid, const float* beta, int n_cams, const mc_camera* cams,
-                       const mc_params* params, double* images, uint32_t first_step, uint32_t n_steps,
-                       uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves,
-                       mc_stats* stats, void* hip_stream) {
+static int capture_gathers(const mc_grid* grid, const float* beta, int n_cams, const mc_camera* cams,
+                           const mc_params* params, double* images, uint32_t first_step, uint32_t n_steps,
+                           uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves, bool view,
+                           int32_t* strides, mc_stats* stats, void* hip_stream) {
     int rc = validate(grid, beta, n_cams, cams, params);
     if (rc != MC_OK) return rc;
     if (params->transport != MC_FP32 || params->tally != MC_TALLY_F64) return MC_ERR_INVALID_ARG;
@@ -2024,12 +2031,30 @@ int mc_capture_gathers(const mc_grid* grid, const float* beta, int n_cams, const
     if ((rc = precheck_device()) != MC_OK) return rc;
     if (!is_device_ptr(beta) || !is_device_ptr(images) || !is_device_ptr(indices) || !is_device_ptr(wave_steps))
         return MC_ERR_INVALID_ARG;
-    CaptureArgs cap{indices, wave_steps, first_step, n_steps, max_waves, 0u};
+    CaptureArgs cap{indices, wave_steps, first_step, n_steps, max_waves, view, 0u, {0, 0, 0}};
     rc = run<float>(MODE_RENDER, grid, beta, n_cams, cams, params, images, nullptr, nullptr, nullptr, stats, 0, 0, 0,
                     nullptr, nullptr, nullptr, static_cast<hipStream_t>(hip_stream), nullptr, nullptr, 0, nullptr,
                     nullptr, nullptr, &cap);
     *n_waves = cap.n_waves;
+    if (strides) std::copy(cap.stride, cap.stride + 3, strides);
     return rc;
+}
+
+int mc_capture_gathers(const mc_grid* grid, const float* beta, int n_cams, const mc_camera* cams,
+                       const mc_params* params, double* images, uint32_t first_step, uint32_t n_steps,
+                       uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves,
+                       mc_stats* stats, void* hip_stream) {
+    return capture_gathers(grid, beta, n_cams, cams, params, images, first_step, n_steps, max_waves, indices,
+                           wave_steps, n_waves, false, nullptr, stats, hip_stream);
+}
+
+int mc_capture_render_gathers(const mc_grid* grid, const float* beta, int n_cams, const mc_camera* cams,
+                              const mc_params* params, double* images, uint32_t first_step, uint32_t n_steps,
+                              uint32_t max_waves, uint32_t* indices, uint32_t* wave_steps, uint32_t* n_waves,
+                              int32_t* strides, mc_stats* stats, void* hip_stream) {
+    if (!strides) return MC_ERR_INVALID_ARG;
+    return capture_gathers(grid, beta, n_cams, cams, params, images, first_step, n_steps, max_waves, indices,
+                           wave_steps, n_waves, true, strides, stats, hip_stream);
 }
 
 int mc_grad_beta(const mc_grid* grid, const void* beta, int n_cams, const mc_camera* cams, const mc_params* params,

@@ -93,7 +93,7 @@ EXPORTS = ["mc_render", "mc_render_moments", "mc_grad_beta", "mc_trace_paths", "
            "mc_voxel_scatter", "mc_voxel_render", "mc_voxel_grad", "mc_voxel_conditioning", "mc_regularizer",
            "mc_image_residual", "mc_gd_step", "mc_camera_noise", "mc_recovery_error", "mc_recover",
            "mc_bmc_render", "mc_render_mixture", "mc_grad_mixture", "mc_render_frozen", "mc_render_noalloc",
-           "mc_capture_gathers"]
+           "mc_capture_gathers", "mc_capture_render_gathers"]
 
 
 class McError(RuntimeError):
@@ -121,6 +121,9 @@ def load_library(path: str = LIB_PATH):
         L.mc_capture_gathers.argtypes = [C.POINTER(McGrid), vp, C.c_int, C.POINTER(McCamera), C.POINTER(McParams),
                                          vp, C.c_uint32, C.c_uint32, C.c_uint32, vp, vp, C.POINTER(C.c_uint32),
                                          C.POINTER(McStats), vp]
+        L.mc_capture_render_gathers.argtypes = [C.POINTER(McGrid), vp, C.c_int, C.POINTER(McCamera),
+                                                C.POINTER(McParams), vp, C.c_uint32, C.c_uint32, C.c_uint32, vp, vp,
+                                                C.POINTER(C.c_uint32), C.POINTER(C.c_int32), C.POINTER(McStats), vp]
         L.mc_render_noalloc.argtypes = [C.POINTER(McGrid), vp, C.c_int, C.POINTER(McCamera),
                                         C.POINTER(McParams), vp, C.POINTER(McStats), vp]
         L.mc_render_moments.argtypes = [C.POINTER(McGrid), vp, C.c_int, C.POINTER(McCamera),
@@ -285,6 +288,26 @@ def mc_capture_gathers(s, beta, first_step, n_steps, max_waves, stream=None, **k
                                            C.byref(st), C.c_void_p(_stream(torch, stream)))
     _check("mc_capture_gathers", rc)
     return idx, steps, int(nw.value), _stats(st)
+
+
+def mc_capture_render_gathers(s, beta, first_step, n_steps, max_waves, stream=None, **kw):
+    """The gather capture on mc_render's own copy of beta: as mc_capture_gathers,
+    with the copy's index steps (x, y, z) before the stats."""
+    torch = _torch()
+    _check_beta(torch, s, beta, "fp32")
+    img = torch.empty(n_pixels(s), dtype=torch.float64, device=beta.device)
+    idx = torch.full((max_waves, n_steps, 64), -1, dtype=torch.int32, device=beta.device)
+    steps = torch.zeros(max_waves, dtype=torch.int32, device=beta.device)
+    nw = C.c_uint32(0)
+    strides = (C.c_int32 * 3)()
+    st = McStats()
+    rc = load_library().mc_capture_render_gathers(
+        C.byref(make_grid(s)), C.c_void_p(beta.data_ptr()), len(s.cameras), make_cameras(s.cameras),
+        C.byref(make_params(s, **kw)), C.c_void_p(img.data_ptr()), int(first_step), int(n_steps), int(max_waves),
+        C.c_void_p(idx.data_ptr()), C.c_void_p(steps.data_ptr()), C.byref(nw), strides, C.byref(st),
+        C.c_void_p(_stream(torch, stream)))
+    _check("mc_capture_render_gathers", rc)
+    return idx, steps, int(nw.value), tuple(strides), _stats(st)
 
 
 def mc_render_moments(s, beta, transport="fp32", tally="f64", stats=True, stream=None, **kw):

@@ -34,29 +34,13 @@ def _lib():
     return L
 
 
-def render_layout(s, k):
-    """Where the render's own copy of beta holds voxel k (int64 tensor; n_vox, the
-    zero word, stays): fastest along the axis that most pixels look along, the
-    other axes in x, y, z order.  (The capture render keeps x fastest.)"""
-    import torch
-    along = [sum(abs(c.R[6 + a]) * c.n_pix for c in s.cameras) for a in range(3)]
-    i = [k % s.nx, (k // s.nx) % s.ny, k // (s.nx * s.ny)]
-    if along[2] >= along[1] and along[2] >= along[0]:
-        m = i[2] + s.nz * (i[0] + s.nx * i[1])
-    elif along[1] > along[0]:
-        m = i[1] + s.ny * (i[0] + s.nx * i[2])
-    else:
-        m = k
-    return torch.where(k == s.n_vox, k, m)
-
-
 def gather_ceiling(s, n_photons, first_step=2000, n_steps=48, reps=20, seed=1000):
     """The render's connection-walk gathers against a replay of the same
     addresses: a capture render (FP32) stores what every lane of every
     wavefront loads on n_steps walk steps from first_step on; the replay
-    kernel issues exactly those loads, moved to where the render's copy of beta
-    holds the voxels, with the same wavefronts per CU and no walk arithmetic,
-    `reps` times over (the rate the vector-memory pipeline
+    kernel issues exactly those loads (the capture walks the render's own copy
+    of beta and its empty runs), with the same wavefronts per CU and no walk
+    arithmetic, `reps` times over (the rate the vector-memory pipeline
     sustains on this address stream and working set).  The render's own rate
     comes from a plain render of the same photons: loads issued by its walks
     (64 per wavefront step, counting the lanes that read zero without an
@@ -71,12 +55,12 @@ def gather_ceiling(s, n_photons, first_step=2000, n_steps=48, reps=20, seed=1000
     sc = s.replace(n_photons=n_photons)
     beta = M.beta_tensor(sc, "fp32")
     max_waves = n_cu * 4 * 4  # four 256-thread blocks per CU, as the render runs
-    idx, steps, nw, cst = M.mc_capture_gathers(sc, beta, first_step, n_steps, max_waves, seed=seed)
+    idx, steps, nw, strides, cst = M.mc_capture_render_gathers(sc, beta, first_step, n_steps, max_waves, seed=seed)
     full = torch.nonzero(steps[:nw] >= first_step + n_steps).flatten()
     nf = (full.numel() // 4) * 4
     if nf < 4:
         raise RuntimeError("no wavefront took enough walk steps for the capture window")
-    sel = render_layout(sc, idx[full[:nf]].long()).int().contiguous()
+    sel = idx[full[:nf]].contiguous()
     # the library's copy of beta: the voxels, then zeros (the zero word and the padding), then one per layer
     data = torch.cat([beta, torch.zeros(64 + sc.nz, dtype=torch.float32, device=dev)])
     sink = torch.zeros(nf * 64, dtype=torch.float32, device=dev)
@@ -95,6 +79,7 @@ def gather_ceiling(s, n_photons, first_step=2000, n_steps=48, reps=20, seed=1000
     issued = (64.0 * wave_steps + rst["vox_free"]) / t
     useful = (rst["vox_conn"] + rst["vox_free"]) / t
     return {"working_set_bytes": 4 * sc.n_vox, "photons": n_photons, "waves_replayed": nf,
+            "index_strides_xyz": list(strides),
             "window_steps": [first_step, first_step + n_steps], "replay_reps": reps, "replay_ms": ms,
             "replay_gloads_per_s": replay / 1e9,
             "render_kernel_ms": rst.timing["transport_ms"],
