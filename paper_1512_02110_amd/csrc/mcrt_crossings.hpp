@@ -9,7 +9,7 @@ namespace mcrt {
 // first minimum is x (then y, then z) advance their index k, their crossing
 // count r and that axis' next crossing t = r g, each axis under its own lane
 // mask (a compare that sets the execution mask; the lanes left go on to the
-// next axis; `more` are further instructions of the z crossing).  15
+// next axis).  15
 // instructions, of which the adds and multiplies take half the issue time of
 // a select: per increment a select against zero and an add, and all three t
 // made anew, took 16 in FP32 and 19 in FP64.  Written out because the

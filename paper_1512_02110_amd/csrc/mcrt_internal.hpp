@@ -173,7 +173,7 @@ constexpr int TILE_VOX = 16384;   // voxels of a gradient tile
 // rounding carries across the tile's x or y face lands in a padding slot,
 // which is never flushed, instead of in another voxel of the tile.
 constexpr int TILE_LDS = 18560;
-constexpr int MAX_TAPE_TILES = 8192;  // per-tile counters of the binning pass: up to 52 KB of LDS
+constexpr int MAX_TAPE_TILES = 8192;  // per-tile counters of the binning pass: with the cameras up to 45 KB of LDS
 constexpr int BIN_LDS_CAMS = 2048;    // camera pixel offsets the binning pass keeps in LDS
 constexpr int BIN_GROUP_TILES = 4096; // tiles per scatter pass (2 LDS words each)
 // Binning blocks of a pass: at least BIN_BLOCKS_PER_CU per compute unit

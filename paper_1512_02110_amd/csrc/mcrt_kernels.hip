@@ -1005,7 +1005,7 @@ __device__ __forceinline__ void drain(const KArgs<Real>& A, const WalkCtx<W>& C,
             }
             qhead += take;
         }
-        // walk until a quarter of the lanes are idle (all, if nothing is
+        // walk until half of the lanes are idle (all, if nothing is
         // queued), in pairs (gradient) or triples of steps (a job always
         // starts with step 0)
         const uint32_t keep = (qtail - qhead) > 0 ? (uint32_t)WAVE - REFILL_IDLE : 0u;
@@ -1690,7 +1690,7 @@ __global__ void __launch_bounds__(DEPOSIT_BLOCK) k_deposit(KArgs<Real> A, const 
         const bool pending = __ballot(has) != 0ull;
         const uint32_t nbusy = (uint32_t)__popcll(__ballot(busy));
         if (!pending && nbusy == 0) break;
-        // walk until a quarter of the lanes are idle while slots are left;
+        // walk until half of the lanes are idle while slots are left;
         // after that, until one more lane is idle (a busy lane may hold the
         // last prefetched records), and at the very end until all are
         const uint32_t keep = more ? (uint32_t)WAVE - DEP_REFILL_IDLE : (pending && nbusy > 0 ? nbusy - 1 : 0u);
@@ -1885,7 +1885,9 @@ __device__ __forceinline__ bool sun_seen(const KArgs<Real>& A, const Photon<Real
 // this takes 1.31 and 4.16 ms (5.0e9 collisions/s).  A launch ends with its
 // longest packet, a serial chain of collisions: with one packet per pixel that
 // chain is the whole 0.38 ms (0.55 before; 0.65 without the idle lanes'
-// help).  Bound by instruction issue and that chain.
+// help).  Bound by instruction issue and that chain.  In FP64 31 registers spill
+// at three wavefronts too (144 bytes a lane); 1, 4 and 16 packets per pixel take
+// 0.68, 1.28 and 2.7 ms (0.94, 2.3 and 6.6 with a packet per lane).
 enum { BMC_NONE = 0, BMC_FLIGHT, BMC_SUN, BMC_HIT, BMC_LIT, BMC_GONE, BMC_DONE, BMC_GO };
 constexpr uint32_t BMC_WAIT = 32;
 
@@ -2756,7 +2758,10 @@ size_t render_dyn_lds(const KArgs<Real>& a, int mode) {
 // the block only (half: 40-70% slower on 64^3), in larger blocks where a
 // wavefront fetches a few times only.  Where the first blocks leave less than a
 // quarter of a block per wavefront, all ids are dealt out evenly: every
-// wavefront would ask for the rest, and most in vain.
+// wavefront would ask for the rest, and most in vain.  Launches that overlap
+// (the gradient's replay chunks, renders on several streams) deal out as much:
+// with blocks only, the replayed gradients of 64^3, 128^3 and 256 x 256 x 128 and
+// renders on three streams take the same time to 0.5%.
 template <typename Real>
 static void set_fetch(KArgs<Real>& a, int grid, int threads, uint64_t n, bool bmc = false) {
     const uint64_t waves = (uint64_t)std::max(grid, 1) * (threads / WAVE), share = n / waves;

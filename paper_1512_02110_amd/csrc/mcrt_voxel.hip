@@ -637,7 +637,10 @@ __device__ __forceinline__ double slab_length(const Slab& B, double vx, double v
 // next ray's length is found: 64^3, 9 cameras of 128^2, 2 x 2 rays 292 us (315
 // with a wait for each) and the near pass's 58, against 3.86 ms of device
 // atomics; 127 x 90 x 77, 16 cameras of 160 x 120 669 (757) + 84 us against
-// 7.6 ms.
+// 7.6 ms.  Wide images, whose voxels beside the camera see many rays that miss:
+// gradients of 64^3 with 9 cameras of 110, 140, 160 and 175 degrees 0.88, 0.88,
+// 0.90 and 0.94 ms, 7.5, 7.7, 6.6 and 4.8 with atomics.  (128 registers, for four
+// wavefronts a SIMD, are ten too few: 44 bytes a lane spill.)
 // COUNT: the number of rays longer than eps.  Otherwise B is used at once: grad(k) += q T j B, and B
 // (scratch) becomes the weight w = T beta j B of the voxel's line of sight, and
 // only the rays of the rectangle of the pixels with dl != 0 are looked at: a
@@ -776,7 +779,7 @@ constexpr int LOS_TILE = 8;
 constexpr int LOS_BLOCK = LOS_TILE * LOS_TILE * LOS_TILE;
 constexpr int LOS_SLICES = 256;
 static_assert(2 * LOS_SLICES <= LOS_BLOCK, "two lanes a slice");
-constexpr int LOS_CELLS = 4608;  // 36 KB: with the tables four blocks a CU
+constexpr int LOS_CELLS = 4608;  // 36 KB: with the tables 41 KB, three blocks a CU (as many as 80 registers allow)
 
 __global__ void __launch_bounds__(LOS_BLOCK, 6) k_vox_los_adjoint(VoxArgs A, int tx, int ty) {
     __shared__ double s_b[LOS_CELLS];
