@@ -1268,7 +1268,10 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
     const int64_t mask_budget = sizeof(Real) == 4 || mixed_render ? MASK_WORDS_FP32 : MASK_WORDS;
     int msh = 0;
     while (((n_vox + ((int64_t)1 << msh) - 1) >> msh) > mask_budget * 32) ++msh;
-    const int64_t mask_words = ((n_vox >> msh) + 1 + 31) / 32;  // (with the zero word's bit)
+    const int64_t run_words = (((n_vox + ((int64_t)1 << msh) - 1) >> msh) + 31) / 32;
+    // (with the zero word's bit: run_words or one more, which the 256 spare
+    // bytes of the scratch hold, so that it takes no input from the fixed one)
+    const int64_t mask_words = ((n_vox >> msh) + 1 + 31) / 32;
 
     // mixed precision: the photons in FP64 (Real = double), the connection
     // rays on a float copy of beta
@@ -1277,7 +1280,7 @@ int run(int mode, const mc_grid* grid, const void* beta, int n_cams, const mc_ca
                    round256(sizeof(Real) * (n_vox + BETA_PAD + grid->nz)) * (beta_eval ? 2 : 1) +
                    round256(sizeof(uint32_t)) +
                    round256(sizeof(DevCam<Real>) * n_cams) + round256(sizeof(NormCam) * n_cams) +
-                   round256(sizeof(uint32_t) * mask_words);
+                   round256(sizeof(uint32_t) * run_words);
     if (mode == MODE_GRAD || mode == MODE_MIXGRAD) bytes += round256(sizeof(double) * n_pix);
     if (mixed) bytes += round256(sizeof(float) * (n_vox + BETA_PAD + grid->nz));
     if (k32 && mode == MODE_RENDER) bytes += round256(sizeof(float) * 2 * n_pix);
